@@ -149,17 +149,18 @@ typedef struct kron_group {
 } kron_group_t;
 
 /* The batched action of Section 2.2 over a batch that mixes sizes and 2-D /
-   3-D operands, in two persistent kernel launches (2-D groups, then 3-D
-   groups; one graph capture holds both).  kron_grouped_prepare builds the
+   3-D operands.  The FP32 groups run in one kernel launch, the bf16x3 groups
+   in another (one graph capture holds both).  kron_grouped_prepare builds the
    plan on the host and copies it into `ws`, caller-owned device memory of
    at least kron_grouped_workspace_size() bytes; it synchronises `stream`.
-   The plan orders each phase's groups, cuts their tiles into chunks that
-   shrink towards the end of the sequence, and holds one counter per phase
-   from which the kernels' wavefronts claim chunks; the last wavefront of a
-   launch resets the counter, so every launch (and graph replay) starts from
-   the prepared state.  Launches that share one `ws` must therefore be
-   ordered (same stream, or synchronised): concurrent ones race on the
-   counter.  Results do not depend on which wavefront ran which chunk.  The
+   The plan gives each FP32 group workgroups in proportion to its cost; of the
+   bf16x3 groups it orders each dimension's, cuts their tiles into chunks that
+   shrink towards the end of the sequence, and holds one counter per dimension
+   from which the wavefronts claim chunks; the last wavefront of a launch
+   resets the counter, so every launch (and graph replay) starts from the
+   prepared state.  Launches that share one `ws` must therefore be ordered
+   (same stream, or synchronised): concurrent ones race on the counter.
+   Results do not depend on which wavefront ran which tiles.  The
    plan keeps the group pointers: the arrays must stay valid while it is
    used.  kron_grouped_launch(ws) runs every group; it is asynchronous and
    takes no host-side work besides the launches.  The plan is bound to this
@@ -537,7 +538,11 @@ int kron_copy_bytes(const void* src, void* dst, size_t bytes, hipStream_t stream
           contiguous rows, the result stores interleaved with the next
           tile's slab loads (window 2/4; otherwise variant 4); 11 = 8 with
           the stores deferred as in 2-D variant 4 (n != 16; otherwise
-          variant 0).  The paper
+          variant 0).
+   blocks_per_cu -1 restores the built-in default.  For 3-D FP32 (n < 16),
+   FP64 and some bf16 sizes that is none of the variants but the column
+   kernels (whole operands in a workgroup's LDS, one column per lane), which
+   kron_get_launch and kron_autotune report as (64, 8).  The paper
    picks its kernel method by matrix size and fixes the number of thread
    blocks (Sections 4 and 5); here the choice is a per-(mode, dim, n) table
    that an autotuner can fill.  Process-wide, not thread-safe against

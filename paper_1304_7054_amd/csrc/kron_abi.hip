@@ -51,11 +51,11 @@ void init_shapes() {
 // Built-in defaults, measured on MI355X at n = 16 with 1 GiB batches (the
 // autotuner refines them per n).
 LaunchShape default_shape(int mode, int dim, int n) {
+  if (dim == 3 && has_cols3d(mode, n)) return LaunchShape{-1, 0};  // the column kernels
   if (n != 16) return LaunchShape{0, dim == 2 ? 3 : 8};  // staged through LDS
   if (dim == 3) {
     switch (mode) {
       case 0: return LaunchShape{2, 9};   // FP32: stores interleaved with the next tile, 2-slab window
-      case 1: return LaunchShape{2, 7};   // FP64: 4-slab window + next tile
       case 2: return LaunchShape{2, 9};   // bf16x3: as FP32
       case 4: return LaunchShape{2, 9};   // bf16x6: as FP32
       default: return LaunchShape{0, 10}; // bf16 storage: stores interleaved, 4-slab window
@@ -738,6 +738,12 @@ const char* kron_status_string(int status) {
   return hipGetErrorString((hipError_t)status);
 }
 
+namespace {
+// The column kernels have no variant number: callers see a pair that the
+// autotuner never tries.
+kron::LaunchShape reported_shape(kron::LaunchShape s) { return s.blocks_per_cu < 0 ? kron::LaunchShape{64, 8} : s; }
+}  // namespace
+
 const char* kron_version(void) { return "kron 0.1 gfx950"; }
 
 int kron_set_launch(int mode, int dim, int n, int blocks_per_cu, int variant) {
@@ -779,7 +785,7 @@ int kron_autotune(int mode, int dim, int n, const void* A, const void* B, const 
     return (int)e;
   }
   // candidate variants: 2-D 0-3 plus 4 (n != 16); 3-D 0-7 plus 9-10
-  // (n = 16) or 8 and 11 (other n)
+  // (n = 16) or 8 and 11 (other n); and the built-in default
   int vars[12], nvar = 0;
   for (int v = 0; v <= (dim == 3 ? 11 : 4); ++v) {
     bool use;
@@ -797,14 +803,14 @@ int kron_autotune(int mode, int dim, int n, const void* A, const void* B, const 
   // a shape whose time varies from launch to launch.  Each timing follows
   // three untimed launches of the same shape.
   constexpr int kSweeps = 3;
-  float times[11 * kNB];
+  float times[11 * kNB + 1];
   for (float& t : times) t = 0.f;
   int rc = 0;
-  const int nshape = nvar * kNB;
+  const int nshape = nvar * kNB + 1;  // the last one: the built-in default
   for (int sweep = 0; sweep < kSweeps && rc == 0; ++sweep) {
     for (int q = 0; q < nshape && rc == 0; ++q) {
       const int idx = sweep % 2 == 0 ? q : nshape - 1 - q;
-      const int v = vars[idx / kNB], b = blocks[idx % kNB];
+      const int v = idx + 1 < nshape ? vars[idx / kNB] : 0, b = idx + 1 < nshape ? blocks[idx % kNB] : -1;
       kron::set_launch_shape(mode, dim, n, b, v);
       for (int w = 0; w < 3 && rc == 0; ++w) rc = run();  // warm-up (first: code object load)
       if (rc != 0) break;
@@ -825,8 +831,8 @@ int kron_autotune(int mode, int dim, int n, const void* A, const void* B, const 
   for (int idx = 0; idx < nshape; ++idx)
     if (times[idx] < best) {
       best = times[idx];
-      bv = vars[idx / kNB];
-      bb = blocks[idx % kNB];
+      bv = idx + 1 < nshape ? vars[idx / kNB] : 0;
+      bb = idx + 1 < nshape ? blocks[idx % kNB] : -1;
     }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
@@ -835,8 +841,9 @@ int kron_autotune(int mode, int dim, int n, const void* A, const void* B, const 
     return rc;
   }
   kron::set_launch_shape(mode, dim, n, bb, bv);
-  if (best_blocks) *best_blocks = bb;
-  if (best_variant) *best_variant = bv;
+  const kron::LaunchShape kept = reported_shape(kron::launch_shape(mode, dim, n));
+  if (best_blocks) *best_blocks = kept.blocks_per_cu;
+  if (best_variant) *best_variant = kept.variant;
   if (best_ms) *best_ms = best;
   return 0;
 }
@@ -847,7 +854,7 @@ int kron_get_launch(int mode, int dim, int n, int* blocks_per_cu, int* variant) 
   if (n < 1 || n > 16) return -3;
   if (!blocks_per_cu) return -4;
   if (!variant) return -5;
-  const kron::LaunchShape sh = kron::launch_shape(mode, dim, n);
+  const kron::LaunchShape sh = reported_shape(kron::launch_shape(mode, dim, n));
   *blocks_per_cu = sh.blocks_per_cu;
   *variant = sh.variant;
   return 0;

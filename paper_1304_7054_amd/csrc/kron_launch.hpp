@@ -7,6 +7,7 @@
 #include <atomic>
 #include <cstdint>
 #include <mutex>
+#include <type_traits>
 #include <unordered_map>
 
 #include "kron_kernels.hpp"
@@ -17,21 +18,21 @@ namespace kron {
 
 // Resident workgroups per CU for a kernel, queried once per kernel (keyed by
 // its address: kernels of one signature must not share the value).
-inline int occupancy_blocks_of(const void* kernel) {
+inline int occupancy_blocks_of(const void* kernel, int threads = kBlock) {
   static std::mutex mu;
   static std::unordered_map<const void*, int> cache;
   std::lock_guard<std::mutex> lock(mu);
   auto it = cache.find(kernel);
   if (it != cache.end()) return it->second;
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, kBlock, 0) != hipSuccess || nb < 1) nb = 1;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, threads, 0) != hipSuccess || nb < 1) nb = 1;
   cache.emplace(kernel, nb);
   return nb;
 }
 
 template <typename K>
-int occupancy_blocks(K kernel) {
-  return occupancy_blocks_of(reinterpret_cast<const void*>(kernel));
+int occupancy_blocks(K kernel, int threads = kBlock) {
+  return occupancy_blocks_of(reinterpret_cast<const void*>(kernel), threads);
 }
 
 // Workgroups to launch: enough to cover the work, at most `per_cu` (or the
@@ -69,6 +70,19 @@ void launch2d_v(int variant, const typename M::io_t* A, const typename M::io_t* 
       launch2d_k<M, N, kTrans, kVec, 4>(A, B, X, Y, batch, ntiles, per_cu, stream);
   }
 }
+
+// Modes and sizes that have a column kernel (kron_cols.hip), by measurement
+// over 1 GiB of operands (old: the best of the other variants):
+//   FP32, n < 16 (at n = 16 one operand fills a 16-slot tile, in registers):
+//     3.1 .. 4.9 -> 4.6 .. 6.0 TB/s (n = 10: 3.87 -> 5.31; n = 7: 3.87 -> 5.24);
+//   FP64, every n: 2.6 .. 4.6 -> 4.5 .. 6.1 TB/s (n = 12: 3.01 -> 5.42; n = 16:
+//     4.60 -> 5.53);
+//   bf16 storage, the sizes whose tiles waste most slots: 2.2 .. 3.4 -> 3.4 ..
+//     4.0 TB/s; at the others the staged tiles' K = 32 products need fewer
+//     matrix cycles than FP32 ones (n = 12: 4.3 against 3.7 TB/s).
+template <class M, int N>
+constexpr bool kHasCols = std::is_same_v<M, ModeF64> || (std::is_same_v<M, ModeF32> && N < 16) ||
+                          (std::is_same_v<M, ModeBF16> && (N == 3 || (N >= 5 && N <= 11 && N != 8)));
 
 // Sizes that read their tiles through LDS: every n but 16 (an FP64 3-D
 // slice is up to 32 KiB per wavefront, 128 KiB per workgroup).
@@ -166,6 +180,7 @@ void launch3d_v(int variant, const typename M::io_t* A, const typename M::io_t* 
 // sizes and unaligned arrays run variant 4, the same stage order), 11 = 8
 // with two LDS slices per wavefront where they fit and each tile's copy-out
 // issued after the next tile's operands are committed (n = 16: variant 0).
+// Workgroups per CU -1: the column kernels.
 template <class M, int N, bool kTrans>
 int launch3d_n(const typename M::io_t* A, const typename M::io_t* B, const typename M::io_t* C,
                const typename M::io_t* X, typename M::io_t* Y, int64_t batch, hipStream_t stream, int mode) {
@@ -173,6 +188,9 @@ int launch3d_n(const typename M::io_t* A, const typename M::io_t* B, const typen
   constexpr int64_t ops = (int64_t)Geo<N>::Q * Geo<N>::Q * Geo<N>::Q;
   const int64_t ntiles = (batch + ops - 1) / ops;
   const LaunchShape sh = launch_shape(mode, 3, N);
+  if constexpr (kHasCols<M, N>) {
+    if (sh.blocks_per_cu < 0) return cols3d(N, A, B, C, X, Y, batch, stream, kTrans);
+  }
   if constexpr (kStageable<M, N, 3>) {
     if (sh.variant == 8 || sh.variant == 11) {
       auto k = sh.variant == 11 ? kron3d_staged_kernel<M, N, kTrans, true> : kron3d_staged_kernel<M, N, kTrans, false>;

@@ -14,7 +14,7 @@ namespace kron {
 int device_cus();
 
 // Launch shape for (mode, dim, n): workgroups per CU (0 = as many as are
-// resident at once) and kernel variant.  Defaults come from a table measured
+// resident at once) and kernel variant; (-1, 0) = the column kernels.  Defaults come from a table measured
 // on MI355X; kron_set_launch / kron_autotune replace them.
 struct LaunchShape {
   int blocks_per_cu;
@@ -65,6 +65,16 @@ int fwd3d_bf16_lo(int n, const uint16_t* A, const uint16_t* B, const uint16_t* C
                 hipStream_t s);
 int fwd3d_bf16_hi(int n, const uint16_t* A, const uint16_t* B, const uint16_t* C, const uint16_t* X, uint16_t* Y, int64_t batch,
                 hipStream_t s);
+
+// 3-D column kernels (kron_cols.hip) of the modes and sizes that have one.
+// cols3d returns 0, or -1 without one.
+bool has_cols3d(int mode, int n);
+int cols3d(int n, const float* A, const float* B, const float* C, const float* X, float* Y, int64_t batch,
+           hipStream_t s, bool trans);
+int cols3d(int n, const double* A, const double* B, const double* C, const double* X, double* Y, int64_t batch,
+           hipStream_t s, bool trans);
+int cols3d(int n, const uint16_t* A, const uint16_t* B, const uint16_t* C, const uint16_t* X, uint16_t* Y,
+           int64_t batch, hipStream_t s, bool trans);
 
 // Y <- K(op(X)) + beta Y (kron_ex_<mode>.hip) for beta != 0 or, in 2-D,
 // transposed operands (transx); alpha and op on the factors are already in
