@@ -450,9 +450,8 @@ int kron1d_batched_f64(int n, char opA, double alpha, const double* A, int lda, 
    overwritten (zero for batch == 0).  Any of dX, dA, dB, dC may be NULL to
    skip it; X may be NULL when only dX is wanted.  dX must not alias X or dY.
    `ws` is caller-owned device memory of at least
-   kron_backward_workspace_size(dim, n, batch, mode) bytes (per-wavefront or
-   per-workgroup partial sums; needed only for dA/dB/dC).  For 3-D n = 16
-   FP32 with 16-byte aligned X, dY and dX and at least one factor gradient
+   kron_backward_workspace_size(dim, n, batch, mode) bytes (per-workgroup
+   partial sums; needed only for dA/dB/dC).  With at least one factor gradient
    requested, dX and the factor gradients come from one pass over X and dY.
    The summation order is fixed, so repeated calls on the same device give
    identical bits.  FP32 partial sums, final sums in FP64.  Asynchronous on

@@ -386,10 +386,9 @@ int kron2d_backward_f32(int n, const float* A, const float* B, const float* X, c
   if (!A) return -2;
   if (!B) return -3;
   if (int rc = check_backward<float>(2, n, X, dY, dX, dA, dB, nullptr, batch, ws, ws_bytes, 4)) return rc;
-  if (dX && batch > 0) {
-    if (int rc = finish_launch(kron::fwd2d_f32(n, A, B, dY, dX, batch, stream, true))) return rc;
-  }
-  if (dA || dB) return finish_launch(kron::grad2d_f32(n, A, B, X, dY, dA, dB, batch, ws, stream));
+  if (dA || dB)
+    return finish_launch(kron::backward(2, n, A, B, nullptr, X, dY, dX, dA, dB, nullptr, batch, ws, stream));
+  if (dX && batch > 0) return finish_launch(kron::fwd2d_f32(n, A, B, dY, dX, batch, stream, true));
   return 0;
 }
 
@@ -401,12 +400,9 @@ int kron3d_backward_f32(int n, const float* A, const float* B, const float* C, c
   if (!B) return -3;
   if (!C) return -4;
   if (int rc = check_backward<float>(3, n, X, dY, dX, dA, dB, dC, batch, ws, ws_bytes, 5)) return rc;
-  if (n == 16 && (dA || dB || dC) && kron::backward3d16_usable(X, dY, dX))
-    return finish_launch(kron::backward3d16_f32(A, B, C, X, dY, dX, dA, dB, dC, batch, ws, stream));
-  if (dX && batch > 0) {
-    if (int rc = finish_launch(kron::fwd3d_f32(n, A, B, C, dY, dX, batch, stream, true))) return rc;
-  }
-  if (dA || dB || dC) return finish_launch(kron::grad3d_f32(n, A, B, C, X, dY, dA, dB, dC, batch, ws, stream));
+  if (dA || dB || dC)
+    return finish_launch(kron::backward(3, n, A, B, C, X, dY, dX, dA, dB, dC, batch, ws, stream));
+  if (dX && batch > 0) return finish_launch(kron::fwd3d_f32(n, A, B, C, dY, dX, batch, stream, true));
   return 0;
 }
 
@@ -416,10 +412,9 @@ int kron2d_backward_f64(int n, const double* A, const double* B, const double* X
   if (!A) return -2;
   if (!B) return -3;
   if (int rc = check_backward<double>(2, n, X, dY, dX, dA, dB, nullptr, batch, ws, ws_bytes, 4)) return rc;
-  if (dX && batch > 0) {
-    if (int rc = finish_launch(kron::fwd2d_f64(n, A, B, dY, dX, batch, stream, true))) return rc;
-  }
-  if (dA || dB) return finish_launch(kron::grad2d_f64(n, A, B, X, dY, dA, dB, batch, ws, stream));
+  if (dA || dB)
+    return finish_launch(kron::backward(2, n, A, B, nullptr, X, dY, dX, dA, dB, nullptr, batch, ws, stream));
+  if (dX && batch > 0) return finish_launch(kron::fwd2d_f64(n, A, B, dY, dX, batch, stream, true));
   return 0;
 }
 
@@ -431,10 +426,9 @@ int kron3d_backward_f64(int n, const double* A, const double* B, const double* C
   if (!B) return -3;
   if (!C) return -4;
   if (int rc = check_backward<double>(3, n, X, dY, dX, dA, dB, dC, batch, ws, ws_bytes, 5)) return rc;
-  if (dX && batch > 0) {
-    if (int rc = finish_launch(kron::fwd3d_f64(n, A, B, C, dY, dX, batch, stream, true))) return rc;
-  }
-  if (dA || dB || dC) return finish_launch(kron::grad3d_f64(n, A, B, C, X, dY, dA, dB, dC, batch, ws, stream));
+  if (dA || dB || dC)
+    return finish_launch(kron::backward(3, n, A, B, C, X, dY, dX, dA, dB, dC, batch, ws, stream));
+  if (dX && batch > 0) return finish_launch(kron::fwd3d_f64(n, A, B, C, dY, dX, batch, stream, true));
   return 0;
 }
 

@@ -1,0 +1,431 @@
+// The whole backward of a batch with shared factors in one pass: dX and the
+// partial sums of dA, dB (, dC), FP32 and FP64, any n.
+//
+// A workgroup holds P operands of X and of D = dY in LDS (the column layout of
+// kron_cols.hpp).  Every factor gradient pairs X, transformed on some axes,
+// with D, transformed on the others, and contracts all columns along the
+// factor's own axis:
+//   3-D  D1 = C^T on the fast axis of D, D2 = B^T on the middle axis of D1,
+//        X1 = A on the slow axis of X, X2 = B on the middle axis of X1:
+//        dA(i, a) = sum D2(i, ..) X(a, ..)      over the slow-axis columns
+//        dB(j, b) = sum D1(j, ..) X1(b, ..)     over the middle-axis columns
+//        dC(k, c) = sum D(k, ..) X2(c, ..)      over the fast-axis columns
+//        dX = A^T on the slow axis of D2
+//   2-D  D1 = B^T on the fast axis of D, X1 = A on the slow axis of X:
+//        dA(i, u) = sum D1(i, ..) X(u, ..),  dB(j, v) = sum D(j, ..) X1(v, ..),
+//        dX = A^T on the slow axis of D1
+// so the chains of X and of D serve all gradients and dX: five products and
+// three contractions in 3-D, where separate gradients take nine and three.
+// Three LDS images (X, D and a work image) suffice, because X1 and D1 wait in
+// registers while the work image holds D2.
+//
+// A contraction takes four columns per 16x16x4 instruction: lane (L, g) reads
+// element L of column g of both images.  Its rows and columns beyond n hold
+// values that no result uses, so only missing columns are masked.
+#pragma once
+
+#include "kron_cols.hpp"
+
+namespace kron {
+
+// Operands per tile, wavefronts per workgroup, and wavefronts per SIMD the
+// registers are held to; measured at 512 MiB of X.  FP32 3-D n = 16: three
+// workgroups of four wavefronts fit a CU (408 us; two of eight: 430).
+struct BwdShape {
+  int ops, waves, per_simd;
+};
+
+template <int Dim, int N, typename T>
+constexpr BwdShape bwd_shape() {
+  constexpr int f3[17] = {0, 256, 64, 28, 16, 10, 7, 5, 4, 3, 2, 2, 1, 1, 1, 1, 1};
+  constexpr int w3[17] = {0, 4, 4, 4, 4, 4, 4, 4, 4, 4, 4, 4, 3, 3, 4, 4, 4};
+  constexpr int d3[17] = {0, 256, 64, 28, 16, 10, 7, 5, 4, 1, 1, 1, 1, 1, 1, 1, 1};
+  constexpr int v3[17] = {0, 4, 4, 4, 4, 4, 4, 4, 4, 4, 4, 4, 5, 6, 7, 8, 8};
+  if (Dim == 3) {
+    if (sizeof(T) == 8) return BwdShape{d3[N], v3[N], 2};
+    return BwdShape{f3[N], w3[N], N <= 8 ? 5 : N <= 12 ? 4 : 3};
+  }
+  if (sizeof(T) == 8) return BwdShape{N <= 8 ? 256 / N : 128 / N, 4, 2};
+  return BwdShape{N < 16 ? 256 / N : 8, 4, N >= 12 && N < 16 ? 3 : 4};
+}
+
+template <typename T, int Dim_, int N_>
+struct Bwd {
+  using io_t = T;
+  static constexpr int Dim = Dim_, N = N_;
+  static constexpr int P = bwd_shape<Dim, N, T>().ops, kWaves = bwd_shape<Dim, N, T>().waves;
+  static constexpr int kThreads = 64 * kWaves;
+  static constexpr int kKind = N == 16 ? kColMatrix : col_kind<N, T>();
+  template <bool kTrans>
+  using Factor = ColFactor<N, kTrans, T, kKind>;
+  static constexpr bool kMat = Factor<false>::kLanes == 16;
+  static constexpr int kE = Factor<false>::kE, kd = kMat && sizeof(T) == 8 ? 4 : 1;
+  static constexpr int E = Dim == 3 ? N * N * N : N * N;
+  static constexpr int NP = Dim == 3 ? P * N : P;  // planes of n rows
+  static constexpr int kCols = NP * N;             // columns along any axis
+  static constexpr int NC = (kCols + Factor<false>::kLanes * kWaves - 1) / (Factor<false>::kLanes * kWaves);
+  static constexpr int NE = (P * E + kThreads - 1) / kThreads;  // elements per thread (2-D loads)
+  // n = 16: row b of a plane holds its groups of four at (group ^ (b / 4)), so
+  // that neither a read along the rows nor one down them meets a bank twice;
+  // with padded rows instead, three images of two workgroups fill a CU, so
+  // three.  Planes at pitches that spread the slow-axis reads.
+  static constexpr int kMinWaves = bwd_shape<Dim, N, T>().per_simd;
+  static constexpr int PL = N == 16 ? 276 : N * N + (N == 8 ? 8 : N == 4 || N == 12 ? 4 : 0);
+  static constexpr int kImage = NP * PL;
+  __device__ static constexpr int swz(int row) { return N == 16 ? 4 * (row >> 2) : 0; }
+  __device__ static constexpr int at(int plane, int row, int col) { return plane * PL + row * N + (col ^ swz(row)); }
+};
+
+template <class S>
+struct BwdTiles {
+  using T = typename S::io_t;
+  static constexpr int N = S::N, P = S::P, NC = S::NC, kE = S::kE, kd = S::kd, PL = S::PL, kT = S::kThreads;
+  using acc_t = std::conditional_t<sizeof(T) == 8, f64x4, f32x4>;
+  typedef T regs_t[NC][kE];
+
+  const int tid, wave, k0, q0;
+  int plane1[NC], fast1[NC];  // column q as (plane, position) of the middle and fast axes
+  int op0[NC], row0[NC], col0[NC];  // 3-D slow-axis column: operand, row, position
+  bool ok[NC];
+
+  __device__ __forceinline__ BwdTiles()
+      : tid(threadIdx.x),
+        wave(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)),
+        k0(S::kMat ? ((threadIdx.x & 63) >> 4) * (kd == 4 ? 1 : 4) : 0),
+        q0(S::kMat ? 16 * (threadIdx.x >> 6) + (threadIdx.x & 15) : threadIdx.x) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int q = q0 + (S::kMat ? 16 : 64) * S::kWaves * c;
+      ok[c] = q < S::kCols;
+      plane1[c] = q / N;
+      fast1[c] = q % N;
+      op0[c] = q / (N * N);
+      row0[c] = q / N % N;
+      col0[c] = q % N;
+    }
+  }
+
+  __device__ __forceinline__ bool has(int s) const { return !S::kMat || N % 4 == 0 || s + 1 < kE || k0 + kd * s < N; }
+
+  // LDS offset of element s of column c along an axis: 0 the fast one, 1 the
+  // one above it (3-D: middle, 2-D: slow), 2 the 3-D slow one.
+  template <int kAxis>
+  __device__ __forceinline__ int where(int c, int s) const {
+    const int k = k0 + kd * s;
+    if constexpr (kAxis == 0) return plane1[c] * PL + fast1[c] * N + (k ^ S::swz(fast1[c]));
+    if constexpr (kAxis == 1) return plane1[c] * PL + k * N + (fast1[c] ^ S::swz(k));
+    return (op0[c] * N + k) * PL + row0[c] * N + (col0[c] ^ S::swz(row0[c]));
+  }
+  template <int kAxis>
+  __device__ __forceinline__ void get(const T* img, regs_t& z) const {
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (ok[c]) {
+        if constexpr (kAxis == 0 && N % 4 == 0 && sizeof(T) == 4) {
+#pragma unroll
+          for (int s = 0; s < kE; s += 4) {
+            const f32x4 v = *in_lds(reinterpret_cast<const f32x4*>(img + where<0>(c, s)));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) z[c][s + j] = v[j];
+          }
+        } else {
+#pragma unroll
+          for (int s = 0; s < kE; ++s) z[c][s] = has(s) ? in_lds(img)[where<kAxis>(c, s)] : T(0);
+        }
+      }
+  }
+  template <int kAxis>
+  __device__ __forceinline__ void put(T* img, const regs_t& z) const {
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (ok[c]) {
+        if constexpr (kAxis == 0 && N % 4 == 0 && sizeof(T) == 4) {
+#pragma unroll
+          for (int s = 0; s < kE; s += 4)
+            *in_lds(reinterpret_cast<f32x4*>(img + where<0>(c, s))) = f32x4{z[c][s], z[c][s + 1], z[c][s + 2], z[c][s + 3]};
+        } else {
+#pragma unroll
+          for (int s = 0; s < kE; ++s)
+            if (has(s)) in_lds(img)[where<kAxis>(c, s)] = z[c][s];
+        }
+      }
+  }
+
+  // acc += sum over the columns of the tile's first `planes` planes (3-D slow
+  // axis: rows) of U(L, column) V(L, column).  The wavefronts take planes in
+  // turn.  A tile's columns are summed by themselves first, in two chains that
+  // keep the matrix pipe fed, so that the running sum grows by one rounding per
+  // tile instead of one per column.
+  template <int kAxis>
+  __device__ __forceinline__ void contract(const T* U, const T* V, int planes, acc_t& sum) const {
+    acc_t acc[2] = {acc_t{0, 0, 0, 0}, acc_t{0, 0, 0, 0}};
+    add_columns<kAxis>(U, V, planes, acc);
+    sum += acc[0] + acc[1];
+  }
+  template <int kAxis>
+  __device__ __forceinline__ void add_columns(const T* U, const T* V, int planes, acc_t (&acc)[2]) const {
+    const int l = threadIdx.x & 63, g = l >> 4, L = (l & 15) < N ? (l & 15) : N - 1;
+    constexpr int G = (N + 3) / 4;
+    if constexpr (N == 16 && kAxis != 0) {
+      // columns 4g .. 4g + 3 of a row are consecutive: one vector per image
+      typedef T vec_t __attribute__((ext_vector_type(4)));
+      for (int r = wave; r < planes; r += S::kWaves) {
+        const int e = kAxis == 1 ? S::at(r, L, 4 * g) : r / N * (N * PL) + S::at(L, r % N, 4 * g);
+        const vec_t u = *in_lds(reinterpret_cast<const vec_t*>(U + e)), v = *in_lds(reinterpret_cast<const vec_t*>(V + e));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if constexpr (sizeof(T) == 8) acc[j & 1] = mfma_f64(u[j], v[j], acc[j & 1]);
+          else acc[j & 1] = mfma_f32(u[j], v[j], acc[j & 1]);
+        }
+      }
+      return;
+    }
+    int lane[G];
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+      if constexpr (kAxis == 0) lane[j] = (4 * j + g < N ? 4 * j + g : 0) * N + (L ^ S::swz(4 * j));
+      else if constexpr (kAxis == 1) lane[j] = L * N + ((4 * j) ^ S::swz(L)) + g;
+      else lane[j] = L * PL + g;
+    }
+    for (int r = wave; r < planes; r += S::kWaves) {
+      int off, sw = 0;
+      if constexpr (kAxis == 2) {
+        const int p = r / N, b = r % N;
+        off = p * N * PL + b * N;
+        sw = S::swz(b);
+      } else {
+        off = r * PL;
+      }
+#pragma unroll
+      for (int j = 0; j < G; ++j) {
+        int e = lane[j] + off;
+        if constexpr (kAxis == 2) e += (4 * j) ^ sw;
+        T u, v;
+        if (N % 4 != 0 && j == G - 1) {
+          const bool in = 4 * j + g < N;
+          u = in ? in_lds(U)[e] : T(0);
+          v = in ? in_lds(V)[e] : T(0);
+        } else {
+          u = in_lds(U)[e];
+          v = in_lds(V)[e];
+        }
+        if constexpr (sizeof(T) == 8) acc[j & 1] = mfma_f64(u, v, acc[j & 1]);
+        else acc[j & 1] = mfma_f32(u, v, acc[j & 1]);
+      }
+    }
+  }
+
+  // 3-D: the slow-axis columns of tile t of an array
+  __device__ __forceinline__ void load_cols(const T* A, int64_t t, int64_t batch, regs_t& z) const {
+    const T* At = A + t * (int64_t)(P * S::E);
+    const int64_t rem = batch - t * P;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (ok[c] && op0[c] < rem) {
+#pragma unroll
+        for (int s = 0; s < kE; ++s)
+          if (has(s)) z[c][s] = in_global(At)[op0[c] * S::E + (k0 + kd * s) * N * N + row0[c] * N + col0[c]];
+      }
+  }
+  __device__ __forceinline__ void store_cols(T* A, int64_t t, int64_t batch, const regs_t& z) const {
+    T* At = A + t * (int64_t)(P * S::E);
+    const int64_t rem = batch - t * P;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (ok[c] && op0[c] < rem) {
+#pragma unroll
+        for (int s = 0; s < kE; ++s)
+          if (has(s)) in_global(At)[op0[c] * S::E + (k0 + kd * s) * N * N + row0[c] * N + col0[c]] = z[c][s];
+      }
+  }
+  // 2-D: the tile's elements in memory order, consecutive lanes
+  __device__ __forceinline__ void load_flat(const T* A, int64_t t, int count, T (&r)[S::NE]) const {
+#pragma unroll
+    for (int i = 0; i < S::NE; ++i) {
+      const int e = tid + kT * i;
+      if (e < count) r[i] = in_global(A + t * (int64_t)(P * S::E))[e];
+    }
+  }
+  __device__ __forceinline__ static int flat(int e) { return S::at(e / (N * N), e / N % N, e % N); }
+};
+
+// `which` bit f asks for factor f's gradient; dX may be null (then some
+// gradient is wanted).  Partials: ws[(block * 3 + f) * 256 + row * 16 + col].
+template <class S>
+__global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::kMinWaves))) void kron_backward_kernel(
+    const typename S::io_t* __restrict__ A, const typename S::io_t* __restrict__ B,
+    const typename S::io_t* __restrict__ C, const typename S::io_t* __restrict__ X,
+    const typename S::io_t* __restrict__ dY, typename S::io_t* __restrict__ dX, typename S::io_t* __restrict__ ws,
+    int64_t batch, int64_t ntiles, int which) {
+  using T = typename S::io_t;
+  using Tiles = BwdTiles<S>;
+  constexpr int N = S::N, P = S::P, NC = S::NC, kE = S::kE, Dim = S::Dim, kWaves = S::kWaves;
+  constexpr int kRed = kWaves * Dim * 256;  // the wavefronts' sums, at the end
+  __shared__ __attribute__((aligned(16))) T lds[3 * S::kImage > kRed ? 3 * S::kImage : kRed];
+  T* const ix = lds;
+  T* const id = lds + S::kImage;
+  T* const iw = lds + 2 * S::kImage;
+  const Tiles tl;
+  const int lane = threadIdx.x & 63;
+  typename Tiles::acc_t acc[Dim];
+#pragma unroll
+  for (int f = 0; f < Dim; ++f) acc[f] = typename Tiles::acc_t{0, 0, 0, 0};
+  const bool wa = which & 1, wb = which & 2, wc = which & 4;
+  const typename S::template Factor<false> fA(A, lane);
+  const typename S::template Factor<true> tA(A, lane), tB(B, lane);
+  T z[NC][kE] = {}, x1[NC][kE] = {};
+  if constexpr (Dim == 3) {
+    const typename S::template Factor<false> fB(B, lane);
+    const typename S::template Factor<true> tC(C, lane);
+    T x[NC][kE] = {}, d[NC][kE] = {}, d1[NC][kE] = {};
+    int64_t t = blockIdx.x;
+    if (t < ntiles) {
+      if (which) tl.load_cols(X, t, batch, x);
+      tl.load_cols(dY, t, batch, d);
+    }
+    for (; t < ntiles; t += gridDim.x) {
+      const int64_t rem = batch - t * P;
+      const int planes = (int)(rem < P ? rem : P) * N;
+      lds_barrier();  // every wavefront is done with the previous tile's images
+      tl.template put<2>(id, d);
+      if (which) {
+        tl.template put<2>(ix, x);
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int s = 0; s < kE; ++s) x1[c][s] = x[c][s];
+        fA.template apply<NC>(x1);
+      }
+      lds_barrier();
+      if (t + gridDim.x < ntiles) {
+        if (which) tl.load_cols(X, t + gridDim.x, batch, x);
+        tl.load_cols(dY, t + gridDim.x, batch, d);
+      }
+      tl.template get<0>(id, d1);
+      tC.template apply<NC>(d1);
+      tl.template put<0>(iw, d1);
+      lds_barrier();
+      if (wa || dX) {
+        tl.template get<1>(iw, z);
+        tB.template apply<NC>(z);
+        tl.template put<1>(iw, z);
+        lds_barrier();
+        if (wa) tl.template contract<2>(iw, ix, planes, acc[0]);
+        if (dX) {
+          tl.template get<2>(iw, z);
+          tA.template apply<NC>(z);
+          tl.store_cols(dX, t, batch, z);
+        }
+        if (!(wb || wc)) continue;
+        lds_barrier();
+        if (wb) tl.template put<0>(iw, d1);
+      }
+      tl.template put<2>(ix, x1);
+      lds_barrier();
+      if (wb) tl.template contract<1>(iw, ix, planes, acc[1]);
+      if (wc) {
+        tl.template get<1>(ix, z);
+        fB.template apply<NC>(z);
+        lds_barrier();
+        tl.template put<1>(ix, z);
+        lds_barrier();
+        tl.template contract<0>(id, ix, planes, acc[2]);
+      }
+    }
+  } else {
+    T x[S::NE] = {}, d[S::NE] = {};
+    auto count_of = [&](int64_t t) {
+      const int64_t rem = batch - t * P;
+      return (int)(rem < P ? rem : P) * S::E;
+    };
+    int64_t t = blockIdx.x;
+    if (t < ntiles) {
+      if (which) tl.load_flat(X, t, count_of(t), x);
+      tl.load_flat(dY, t, count_of(t), d);
+    }
+    for (; t < ntiles; t += gridDim.x) {
+      const int count = count_of(t), planes = count / S::E;
+      lds_barrier();  // every wavefront is done with the previous tile's images
+#pragma unroll
+      for (int i = 0; i < S::NE; ++i) {
+        const int e = tl.tid + S::kThreads * i;
+        if (e < count) {
+          in_lds(id)[Tiles::flat(e)] = d[i];
+          if (which) in_lds(ix)[Tiles::flat(e)] = x[i];
+        }
+      }
+      lds_barrier();
+      const int64_t tn = t + gridDim.x;
+      if (tn < ntiles) {
+        if (which) tl.load_flat(X, tn, count_of(tn), x);
+        tl.load_flat(dY, tn, count_of(tn), d);
+      }
+      if (wa || dX) {
+        tl.template get<0>(id, z);
+        tB.template apply<NC>(z);
+        tl.template put<0>(iw, z);
+      }
+      if (wb) {
+        tl.template get<1>(ix, x1);
+        fA.template apply<NC>(x1);
+      }
+      lds_barrier();
+      if (wa) tl.template contract<1>(iw, ix, planes, acc[0]);
+      if (dX) {
+        tl.template get<1>(iw, z);
+        tA.template apply<NC>(z);
+      }
+      lds_barrier();
+      if (dX) tl.template put<1>(iw, z);
+      if (wb) tl.template put<1>(ix, x1);
+      lds_barrier();
+      if (wb) tl.template contract<0>(id, ix, planes, acc[1]);
+      if (dX) {
+        T* dXt = dX + t * (int64_t)(P * S::E);
+        for (int e = tl.tid; e < count; e += S::kThreads) in_global(dXt)[e] = in_lds(iw)[Tiles::flat(e)];
+      }
+    }
+  }
+  if (which == 0) return;
+  // the wavefronts' partials, summed in wavefront order through LDS
+  lds_barrier();
+  const int g = lane >> 4, L = lane & 15;
+#pragma unroll
+  for (int f = 0; f < Dim; ++f)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      in_lds(lds)[(tl.wave * Dim + f) * 256 + (sizeof(T) == 8 ? g + 4 * r : 4 * g + r) * 16 + L] = acc[f][r];
+  lds_barrier();
+  for (int e = tl.tid; e < Dim * 256; e += S::kThreads) {
+    T sum = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) sum += in_lds(lds)[w * Dim * 256 + e];
+    ws[(int64_t)blockIdx.x * 3 * 256 + e] = sum;
+  }
+}
+
+// dM(i, j) = sum of entry (i, j) over the partial tiles, in a fixed order in
+// FP64: one workgroup per entry of each factor, thread t sums partials t,
+// t + 256, .. and a fixed-shape tree finishes.  Column-major (i + n*j).
+template <typename T, int N>
+__global__ __launch_bounds__(256) void kron_backward_sum_kernel(const T* __restrict__ ws, int64_t nparts,
+                                                                T* __restrict__ dA, T* __restrict__ dB,
+                                                                T* __restrict__ dC) {
+  const int f = blockIdx.x / (N * N), e = blockIdx.x % (N * N);
+  T* out = f == 0 ? dA : f == 1 ? dB : dC;
+  if (out == nullptr) return;
+  const int i = e % N, j = e / N;
+  double s = 0.0;
+  for (int64_t w = threadIdx.x; w < nparts; w += 256) s += (double)ws[(w * 3 + f) * 256 + i * 16 + j];
+  __shared__ double red[256];
+  red[threadIdx.x] = s;
+  __syncthreads();
+#pragma unroll
+  for (int h = 128; h > 0; h >>= 1) {
+    if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) out[e] = (T)red[0];
+}
+
+}  // namespace kron

@@ -162,6 +162,37 @@ struct ColFactor<N, kTrans, double, kColMatrix> {
   }
 };
 
+// FP32 on the 16x16x4 instruction: lane (L, g) holds elements 4g .. 4g + 3 of
+// column L, again both operand and result.
+template <int N, bool kTrans>
+struct ColFactor<N, kTrans, float, kColMatrix> {
+  static_assert(N == 16, "every lane's four elements exist");
+  static constexpr int kE = 4, kLanes = 16;
+  float v[kE];
+
+  __device__ __forceinline__ ColFactor(const float* M, int lane) {
+    const int row = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int s = 0; s < kE; ++s) v[s] = in_global(M)[kTrans ? 4 * g + s + N * row : row + N * (4 * g + s)];
+  }
+
+  template <int NC>
+  __device__ __forceinline__ void apply(float (&x)[NC][kE]) const {
+    f32x4 y[NC];
+#pragma unroll
+    for (int s = 0; s < kE; ++s)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        if (s == 0) y[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+        y[c] = mfma_f32(v[s], x[c][s], y[c]);
+      }
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int s = 0; s < kE; ++s) x[c][s] = y[c][s];
+  }
+};
+
 template <int N, typename io_t>
 constexpr int col_kind() {
   return sizeof(io_t) != 8 ? 0 : N <= 8 ? kColScalar : kColMatrix;

@@ -94,21 +94,14 @@ size_t grouped_workspace_bytes(const struct kron_group* g, int ngroups);
 int grouped_prepare(const struct kron_group* g, int ngroups, void* ws, size_t ws_bytes, hipStream_t stream);
 int grouped_launch(const void* ws, hipStream_t stream);
 
-// Factor gradients (kron_grad.hip).  ws holds grad_workspace_bytes().
+// The backward with at least one factor gradient (kron_backward.hip): dX (may
+// be null) and the factor gradients (null ones are skipped; dC only in 3-D) in
+// one pass over X and dY.  ws holds grad_workspace_bytes().
 int64_t grad_waves(int dim, int n, int64_t batch);
 size_t grad_workspace_bytes(int dim, int n, int64_t batch, int elem_bytes);
-int grad2d_f32(int n, const float* A, const float* B, const float* X, const float* dY, float* dA, float* dB,
-               int64_t batch, void* ws, hipStream_t s);
-int grad3d_f32(int n, const float* A, const float* B, const float* C, const float* X, const float* dY, float* dA,
-               float* dB, float* dC, int64_t batch, void* ws, hipStream_t s);
-// 3-D n = 16 FP32 backward in one pass (dX and the factor gradients); usable
-// when X, dY and dX (if given) are 16-byte aligned.
-int backward3d16_f32(const float* A, const float* B, const float* C, const float* X, const float* dY, float* dX,
-                     float* dA, float* dB, float* dC, int64_t batch, void* ws, hipStream_t stream);
-bool backward3d16_usable(const void* X, const void* dY, const void* dX);
-int grad2d_f64(int n, const double* A, const double* B, const double* X, const double* dY, double* dA, double* dB,
-               int64_t batch, void* ws, hipStream_t s);
-int grad3d_f64(int n, const double* A, const double* B, const double* C, const double* X, const double* dY,
-               double* dA, double* dB, double* dC, int64_t batch, void* ws, hipStream_t s);
+int backward(int dim, int n, const float* A, const float* B, const float* C, const float* X, const float* dY,
+             float* dX, float* dA, float* dB, float* dC, int64_t batch, void* ws, hipStream_t s);
+int backward(int dim, int n, const double* A, const double* B, const double* C, const double* X, const double* dY,
+             double* dX, double* dA, double* dB, double* dC, int64_t batch, void* ws, hipStream_t s);
 
 }  // namespace kron

@@ -1,0 +1,46 @@
+"""GPU parity of the one-pass backward for every subset of the outputs (each
+takes other branches of the tile loop) at a single operand, ragged tiles and
+several tiles per workgroup, against the FP64 oracle gradient.  Skipped
+outputs are not passed; tolerances are those of the backward tests."""
+import itertools
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("dim,n", [(2, 1), (2, 5), (2, 13), (2, 16), (3, 2), (3, 8), (3, 11), (3, 16)])
+def test_backward_output_subsets(prec, dim, n):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1304_7054_amd as kron
+    dtype = np.float32 if prec == "f32" else np.float64
+    mode = kron.MODE_F32 if prec == "f32" else kron.MODE_F64
+    fn = getattr(kron, f"kron{dim}d_backward_{prec}")
+    tol = 1e-5 if prec == "f32" else 1e-12
+    subsets = [w for w in itertools.product((False, True), repeat=dim + 1) if any(w)]
+    for k, want in enumerate(subsets):
+        # the first subsets at one operand and at a ragged second tile, the last (all outputs) at many tiles
+        for batch in (1, 259) if k < len(subsets) - 1 else (3, 3_000_000 // n ** dim):
+            rng = np.random.default_rng(100 * n + batch + k)
+            mats = [rng.uniform(-1, 1, n * n).astype(dtype) for _ in range(dim)]
+            X = rng.standard_normal(batch * n ** dim).astype(dtype)
+            dY = rng.standard_normal(batch * n ** dim).astype(dtype)
+            dev = [torch.from_numpy(a).cuda() for a in mats + [X, dY]]
+            dX = torch.full_like(dev[-1], float("nan")) if want[0] else None
+            grads = [torch.full_like(dev[0], float("nan")) if w else None for w in want[1:]]
+            ws = torch.empty(max(1, kron.kron_backward_workspace_size(dim, n, batch, mode)), dtype=torch.uint8,
+                             device="cuda")
+            fn(n, *dev, dX, *grads, batch, ws)
+            torch.cuda.synchronize()
+            wide = [a.astype(np.float64) for a in mats + [X, dY]]
+            ref = (oracle.kron2d_grad if dim == 2 else oracle.kron3d_grad)(n, *wide, batch)
+            for name, got, exact in zip(("dX", "dA", "dB", "dC"), [dX] + grads, ref):
+                if got is not None:
+                    err = np.linalg.norm(got.cpu().numpy() - exact) / np.linalg.norm(exact)
+                    assert err <= tol, (want, batch, name, err)
