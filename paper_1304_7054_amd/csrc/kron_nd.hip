@@ -23,10 +23,13 @@
 // a tile's columns never straddle two operands.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
 #include <cstdint>
 
 #include "kron.h"
 #include "kron_launch.hpp"
+#include "kron_nd_fused.hpp"
 
 namespace kron {
 namespace {
@@ -687,6 +690,218 @@ NdIndex strided_index(int d, const int* ext, const NdStrides& st, int k0) {
   return ix;
 }
 
+// ---- several products in one kernel ----------------------------------------------
+
+// LDS a workgroup may take: two fit a CU.  (With one, 3-D n = 20 FP64 at 256
+// MiB took 379 us; its two fastest products fused and a pass for the third, 349.)
+constexpr size_t kFuseLds = 80 * 1024;
+// Image bytes of a tile of several operands: a few KiB per wavefront, so that
+// several workgroups share a CU.
+constexpr size_t kFuseTile = 20 * 1024;
+
+// Column blocks of 16 a wavefront takes at a time.
+template <typename T, bool kC>
+constexpr int fuse_blocks() {
+  return kC && sizeof(T) == 8 ? 1 : 2;
+}
+
+// Pitch of rows of f elements such that 16 of them, read side by side at the
+// same positions by four lane groups, fall on different banks: 4 words modulo
+// 8 (in elements of 1, 2 or 4 words: 4 mod 8, 2 mod 4, odd).
+int fuse_pitch(int f, size_t elem) {
+  const int w = (int)(elem / 4), mod = 8 / w, want = 4 / w;
+  return mod >= 2 ? f + ((want - f) % mod + mod) % mod : f | 1;
+}
+
+// Plan of the products over indices k0 .. d - 1 as one kernel; false when they
+// do not fit.  Fills everything but the arrays' addresses and strides.
+bool fuse_plan(int d, int k0, const int* m, const int* n, const int* opc, const int* ldf, const int64_t* ldfp,
+               int64_t batch, size_t elem, bool cplx, int blocks, FusedArgs& P, int& ks_max, size_t& lds) {
+  const int ns = d - k0;
+  if (ns < 2 || ns > kFuseMax) return false;
+  P = FusedArgs{};
+  P.nstage = ns;
+  P.per = 1;
+  for (int j = 0; j < k0; ++j) P.per *= n[j];
+  const int64_t slices = batch * P.per;
+  for (int k = k0; k < d; ++k) P.per_operand |= ldfp[k] != 0;
+  // elements of each array of a slice, and the image it is in
+  double elems[kFuseMax + 1];
+  int image[kFuseMax + 1];
+  double size[2] = {0, 0};
+  ks_max = 0;
+  double fac = 0;
+  for (int q = 0; q <= ns; ++q) {
+    double e = 1;
+    for (int j = k0; j < d - 1; ++j) e *= j < d - q ? n[j] : m[j];
+    e *= fuse_pitch(q == 0 ? n[d - 1] : m[d - 1], elem);
+    elems[q] = e;
+    image[q] = q == 0 ? 0 : n[d - q] == m[d - q] ? image[q - 1] : 1 - image[q - 1];
+    size[image[q]] = std::max(size[image[q]], e);
+    if (q < ns) {
+      const int k = d - 1 - q;
+      // (complex products of more than 32 indices measured 4 % slower fused)
+      if (n[k] > (cplx ? 32 : 64) || m[k] > 1024) return false;
+      fac += (double)((m[k] + 15) / 16) * ((n[k] + 3) / 4) * 64;
+      ks_max = std::max(ks_max, (n[k] + 3) / 4);
+    }
+  }
+  // 16-byte aligned images
+  for (double& v : size) v = std::ceil(v / 4) * 4;
+  // an operand's images and its columns' entries in the offset table
+  double cols = 0;
+  for (int k = k0; k < d; ++k) {
+    double c = 1;
+    for (int j = k0; j < d; ++j) c *= j < k ? n[j] : j > k ? m[j] : 1;
+    cols += c;
+  }
+  const double images = (size[0] + size[1]) * (double)elem;
+  const bool table = fac * (double)elem + images + 4 * cols <= (double)kFuseLds;
+  const double one = images + (table ? 4 * cols : 0);
+  if (fac * (double)elem + one > (double)kFuseLds) return false;
+  int64_t ops = 1;
+  if (!P.per_operand) {
+    ops = std::min<int64_t>((int64_t)((double)kFuseTile / one), (int64_t)(((double)kFuseLds - fac * (double)elem) / one));
+    ops = std::min(ops, slices / (2 * device_cus()));  // tiles for every CU first
+    // of those, the count whose column blocks fill the four wavefronts' rounds best
+    const int64_t most = std::max<int64_t>(ops, 1);
+    double best = 1e300;
+    for (int64_t o = 1; o <= most; ++o) {
+      double cost = 0;
+      for (int k = k0; k < d; ++k) {
+        int64_t cols = o;
+        for (int j = k0; j < d; ++j) cols *= j < k ? n[j] : j > k ? m[j] : 1;
+        const int64_t rounds = ((cols + 15) / 16 + 4 * blocks - 1) / (4 * blocks);
+        cost += (double)rounds * ((m[k] + 15) / 16) * ((n[k] + 3) / 4);
+      }
+      if (cost / (double)o <= best) {
+        best = cost / (double)o;
+        ops = o;
+      }
+    }
+  }
+  P.ops = (int)ops;
+  P.batch = slices;
+  P.ntiles = (slices + ops - 1) / ops;
+  int at = 0, tab = 0;
+  const int base[2] = {(int)fac, (int)fac + (int)(ops * size[0])};
+  P.img_x = base[0];
+  P.img_y = base[image[ns]];
+  for (int q = 0; q < ns; ++q) {
+    const int k = d - 1 - q;
+    FusedStage& st = P.st[q];
+    st.n = n[k];
+    st.m = m[k];
+    st.ks = (n[k] + 3) / 4;
+    st.rb = (m[k] + 15) / 16;
+    int pre = 1, post = 1;
+    for (int j = k0; j < k; ++j) pre *= n[j];
+    for (int j = k + 1; j < d; ++j) post *= m[j];
+    st.cols = pre * post;
+    st.post = fast_div((uint32_t)post);
+    if (q == 0) {
+      st.in_u = fuse_pitch(n[k], elem);
+      st.out_u = fuse_pitch(m[k], elem);
+      st.in_s = st.out_s = 1;
+      st.fast = fast_div(1);
+      st.pitch = 0;
+    } else {
+      st.pitch = fuse_pitch(m[d - 1], elem);
+      st.fast = fast_div((uint32_t)m[d - 1]);
+      st.in_s = st.out_s = post / m[d - 1] * st.pitch;
+      st.in_u = n[k] * st.in_s;
+      st.out_u = m[k] * st.out_s;
+    }
+    st.in = base[image[q]];
+    st.out = base[image[q + 1]];
+    st.tab = tab;
+    tab += (int)ops * st.cols;
+    st.fac = at;
+    at += st.rb * st.ks * 64;
+    st.ldfp = ldfp[k];
+    st.ld = ldf[k];
+    st.op = opc[k];
+  }
+  lds = (size_t)(base[1] + (int)(ops * size[1])) * elem;
+  P.table = -1;
+  if (table) {
+    P.table = (int)lds;
+    lds += 4 * (size_t)tab;
+  }
+  return true;
+}
+
+// Real 2-D and 3-D operands of equal extents up to 16, packed, with shared
+// factors: the kernels of the plain and extended entry points on factors
+// prepared in the workspace.
+template <typename T>
+bool nd_plain(int d, const int* m, const int* n, const int* opc, T alpha, const T* const* F, const int* ldf,
+              const int64_t* ldfp, const T* X, T beta, T* Y, int64_t batch, void* ws, size_t need, hipStream_t stream) {
+  if (d != 2 && d != 3) return false;
+  const int N = n[0];
+  if (N > KRON_MAX_N) return false;
+  for (int k = 0; k < d; ++k)
+    if (m[k] != N || n[k] != N || ldfp[k] != 0) return false;
+  if (need < (size_t)d * N * N * sizeof(T)) return false;
+  unsigned tmask = 0;
+  for (int k = 0; k < d; ++k) tmask |= opc[k] != 0 ? 1u << k : 0u;
+  T* P = static_cast<T*>(ws);
+  prepare_factors(N, d, F, ldf, tmask, alpha, P, stream);
+  const T *A = P, *B = P + N * N, *C = P + 2 * N * N;
+  if (beta != T(0)) {
+    if constexpr (sizeof(T) == 8) d == 2 ? ex2d_f64(N, A, B, X, Y, batch, beta, false, stream) : ex3d_f64(N, A, B, C, X, Y, batch, beta, stream);
+    else d == 2 ? ex2d_f32(N, A, B, X, Y, batch, beta, false, stream) : ex3d_f32(N, A, B, C, X, Y, batch, beta, stream);
+  } else {
+    if constexpr (sizeof(T) == 8) d == 2 ? fwd2d_f64(N, A, B, X, Y, batch, stream, false) : fwd3d_f64(N, A, B, C, X, Y, batch, stream, false);
+    else d == 2 ? fwd2d_f32(N, A, B, X, Y, batch, stream, false) : fwd3d_f32(N, A, B, C, X, Y, batch, stream, false);
+  }
+  return true;
+}
+
+bool packed(int d, const int* ext, const NdStrides* st);
+
+template <typename T, bool kC, int kKS, int kCB>
+void fuse_launch(const FusedArgs& P, size_t lds, bool beta, T ar, T ai, T br, T bi, hipStream_t stream) {
+  auto k = beta ? kron_nd_fused_kernel<T, kC, kKS, kCB, true> : kron_nd_fused_kernel<T, kC, kKS, kCB, false>;
+  const int64_t per_cu = std::min<int64_t>(8, 160 * 1024 / (int64_t)lds);
+  const int64_t cap = (int64_t)device_cus() * per_cu;
+  hipLaunchKernelGGL(k, dim3((unsigned)std::min(P.ntiles, cap)), dim3(256), lds, stream, P,
+                     fast_div((uint32_t)P.x.elems), fast_div((uint32_t)P.y.elems), ar, ai, br, bi);
+}
+
+template <typename T, bool kC>
+void fuse_run(const FusedArgs& P, int ks, size_t lds, bool beta, T ar, T ai, T br, T bi, hipStream_t stream) {
+  constexpr int kCB = fuse_blocks<T, kC>();
+  if (ks <= 4) fuse_launch<T, kC, 4, kCB>(P, lds, beta, ar, ai, br, bi, stream);
+  else if (ks <= 8) fuse_launch<T, kC, 8, kCB>(P, lds, beta, ar, ai, br, bi, stream);
+  else fuse_launch<T, kC, 16, kCB>(P, lds, beta, ar, ai, br, bi, stream);
+}
+
+// Whether the strides (none: yes) are those of packed operands.
+bool packed(int d, const int* ext, const NdStrides* st) {
+  int64_t step = 1;
+  for (int j = d - 1; st && j >= 0; --j) {
+    if (st->s[j] != step && ext[j] != 1) return false;
+    step *= ext[j];
+  }
+  return !st || st->sp == step;
+}
+
+// Storage of one side: dense, or strided over all d indices.
+FusedArray fuse_array(int d, int k0, const int* ext, const NdStrides* st, size_t elem) {
+  FusedArray a{};
+  a.elems = 1;
+  for (int j = k0; j < d; ++j) a.elems *= ext[j];
+  a.pitch = fuse_pitch(ext[d - 1], elem);
+  for (int j = 0; j < 3; ++j) a.ext[j] = fast_div(d - 1 - j >= k0 ? (uint32_t)ext[d - 1 - j] : 1);
+  a.stride[0] = -1;
+  if (!packed(d, ext, st)) {
+    for (int j = 0; j < 3; ++j) a.stride[j] = d - 1 - j >= 0 ? st->s[d - 1 - j] : 0;
+    a.sp = st->sp;
+  }
+  return a;
+}
+
 // Argument positions of kron_nd_batched_*: d 1, m 2, n 3, ops 4, alpha 5,
 // factors 6, ldf 7, ldfp 8, X 9, beta 10, Y 11, batch 12, ws 13, ws_bytes 14.
 // xs / ys: strided storage of X and Y (d <= 3), or nullptr for packed
@@ -724,7 +939,34 @@ int nd_run(int d, const int* m, const int* n, const char* ops, T ar, T ai, const
   const bool has_beta = br != T(0) || bi != T(0);
   const void* in = X;
   int which = 0;
-  for (int k = d - 1; k >= 0; --k) {
+  if constexpr (!kC) {
+    if (packed(d, n, xs) && packed(d, m, ys) &&
+        nd_plain(d, m, n, opc, ar, F, ldf, ldfp, X, br, Y, batch, ws, need, stream))
+      return 0;
+  }
+  // The products over the fastest indices, as many as fit, in one kernel; the
+  // rest one pass each.  (Strided storage and beta concern whole operands.)
+  int last_pass = d - 1;
+  for (int k0 = 0; k0 + 2 <= d; ++k0) {
+    FusedArgs P;
+    int ks;
+    size_t lds;
+    if (k0 > 0 && xs) break;
+    if (!fuse_plan(d, k0, m, n, opc, ldf, ldfp, batch, elem, kC, fuse_blocks<T, kC>(), P, ks, lds)) continue;
+    for (int q = 0; q < P.nstage; ++q) P.st[q].F = F[d - 1 - q];
+    P.X = X;
+    P.Y = k0 == 0 ? static_cast<void*>(Y) : static_cast<void*>(buf[which]);
+    P.conjx = conjx;
+    P.x = fuse_array(d, k0, n, k0 == 0 ? xs : nullptr, elem);
+    P.y = fuse_array(d, k0, m, k0 == 0 ? ys : nullptr, elem);
+    const bool whole = k0 == 0;
+    fuse_run<T, kC>(P, ks, lds, whole && has_beta, whole ? ar : T(1), whole ? ai : T(0), br, bi, stream);
+    in = P.Y;
+    which ^= 1;
+    last_pass = k0 - 1;
+    break;
+  }
+  for (int k = last_pass; k >= 0; --k) {
     NdPass P;
     P.X = in;
     P.Y = k == 0 ? static_cast<void*>(Y) : static_cast<void*>(buf[which]);

@@ -89,6 +89,13 @@ int ex2d_f64(int n, const double* A, const double* B, const double* X, double* Y
 int ex3d_f64(int n, const double* A, const double* B, const double* C, const double* X, double* Y, int64_t batch,
              double beta, hipStream_t s);
 
+// alpha op(F_0), op(F_1)[, op(F_2)] (leading dimensions ld, transposed where
+// tmask has the factor's bit) written dense to out, n^2 elements each.
+void prepare_factors(int n, int nf, const float* const* F, const int* ld, unsigned tmask, float alpha, float* out,
+                     hipStream_t stream);
+void prepare_factors(int n, int nf, const double* const* F, const int* ld, unsigned tmask, double alpha, double* out,
+                     hipStream_t stream);
+
 // Grouped launch (kron_grouped.hip).
 size_t grouped_workspace_bytes(const struct kron_group* g, int ngroups);
 int grouped_prepare(const struct kron_group* g, int ngroups, void* ws, size_t ws_bytes, hipStream_t stream);

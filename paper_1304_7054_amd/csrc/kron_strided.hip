@@ -441,6 +441,18 @@ int strided_call(int dim, int n, const char* ops, typename M::io_t alpha, const 
 }
 
 }  // namespace
+
+void prepare_factors(int n, int nf, const float* const* F, const int* ld, unsigned tmask, float alpha, float* out,
+                     hipStream_t stream) {
+  hipLaunchKernelGGL(prepare_strided_factors_kernel<float>, dim3(1), dim3(256), 0, stream, n, nf, F[0], ld[0], F[1],
+                     ld[1], F[nf - 1], ld[nf - 1], tmask, alpha, out);
+}
+void prepare_factors(int n, int nf, const double* const* F, const int* ld, unsigned tmask, double alpha, double* out,
+                     hipStream_t stream) {
+  hipLaunchKernelGGL(prepare_strided_factors_kernel<double>, dim3(1), dim3(256), 0, stream, n, nf, F[0], ld[0], F[1],
+                     ld[1], F[nf - 1], ld[nf - 1], tmask, alpha, out);
+}
+
 }  // namespace kron
 
 extern "C" {
