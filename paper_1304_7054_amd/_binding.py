@@ -9,6 +9,7 @@ there is no other code path.  If libkron.so is missing, every call raises.
 """
 import ctypes
 import os
+import struct
 
 import numpy as np
 
@@ -203,11 +204,13 @@ def kron_get_launch(mode, dim, n):
 
 
 def _stream(stream):
+    """The raw handle of `stream` (default: the current stream of the current device)."""
     if stream is None:
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
-    if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        if torch.cuda.is_initialized():
+            # torch.cuda.current_stream() builds a Stream object for every call (3 us)
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        return torch.cuda.current_stream().cuda_stream
+    return stream if isinstance(stream, int) else stream.cuda_stream
 
 
 def _scratch(need, device, stream):
@@ -224,23 +227,25 @@ def _scratch(need, device, stream):
 
 
 def _arr(t, dtype, min_numel, what):
+    """The address of a contiguous GPU tensor of at least min_numel elements of
+    dtype (None stays None); raises for anything else."""
+    if isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous() and t.numel() >= min_numel:
+        return t.data_ptr()
     if t is None:
         return None
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{what} must be a torch tensor")
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError(f"{what} must live on the GPU, not {t.device}")
     if t.dtype != dtype:
         raise TypeError(f"{what} must have dtype {dtype}, not {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{what} must be contiguous")
-    if t.numel() < min_numel:
-        raise ValueError(f"{what} holds {t.numel()} elements, needs {min_numel}")
-    return ctypes.c_void_p(t.data_ptr())
+    raise ValueError(f"{what} holds {t.numel()} elements, needs {min_numel}")
 
 
 def _call(name, *args):
-    rc = getattr(lib(), name)(*args)
+    rc = getattr(_LIB or lib(), name)(*args)
     if rc != 0:
         raise KronError(name, rc, status_string(rc))
     return rc
@@ -332,23 +337,49 @@ def _backward_call(name, dim, dtype, mode, n, mats, X, dY, dX, grads, batch, ws,
         raise ValueError(f"n must be in 1..16, got {n}")
     if batch < 0:
         raise ValueError("batch must be >= 0")
-    size = batch * n ** dim
-    pm = [_arr(M, dtype, n * n, f"factor {i}") for i, M in enumerate(mats)]
+    nn, size = n * n, batch * n ** dim
+    pm = [_arr(M, dtype, nn, f"factor {i}") for i, M in enumerate(mats)]
     px = _arr(X, dtype, size, "X")
     pdy = _arr(dY, dtype, size, "dY")
     pdx = _arr(dX, dtype, size, "dX")
-    pg = [_arr(G, dtype, n * n, f"gradient {i}") for i, G in enumerate(grads)]
-    for t in [dX] + list(grads):
-        if t is not None and size > 0 and any(o is not None and t.data_ptr() == o.data_ptr() for o in (X, dY)):
-            raise ValueError("outputs must not alias X or dY")
+    pg = [_arr(G, dtype, nn, f"gradient {i}") for i, G in enumerate(grads)]
+    if size > 0 and any(p is not None and p in (px, pdy) for p in [pdx] + pg):
+        raise ValueError("outputs must not alias X or dY")
     need = kron_backward_workspace_size(dim, n, batch, mode) if any(G is not None for G in grads) else 0
     if need and ws is None:
         ws = _scratch(need, dY.device, stream)
     if need and ws.numel() * ws.element_size() < need:
         raise ValueError(f"workspace must hold {need} bytes")
-    pws = ctypes.c_void_p(ws.data_ptr()) if ws is not None else None
+    pws = ws.data_ptr() if ws is not None else None
     nbytes = ws.numel() * ws.element_size() if ws is not None else 0
     return _call(name, n, *pm, px, pdy, pdx, *pg, batch, pws, nbytes, _stream(stream))
+
+
+def forward_rows(dim, n, mats, X, Y, batch):
+    """The action of row-major factors (column-major ones where only the
+    transposed view is contiguous) on FP32 / FP64 operands, on the current
+    stream.  Returns the column-major factors, one after the other, which the
+    call prepares on the device (unset for an empty batch)."""
+    dtype = X.dtype
+    ops, rows = [], []
+    for M in mats:
+        M = M.detach().resolve_neg()
+        if not M.is_contiguous() and M.t().is_contiguous():
+            ops.append(b"N")
+            M = M.t()
+        else:
+            ops.append(b"T")
+            M = M.contiguous()
+        rows.append(M)
+    cols = torch.empty(dim * n * n, dtype=dtype, device=X.device)
+    size = batch * n ** dim
+    ptrs = [_arr(M, dtype, n * n, "factor") for M in rows]
+    if dim == 2:
+        ops.append(b"N")  # op on the operands
+    tag = "f32" if dtype == torch.float32 else "f64"
+    _call(f"kron{dim}d_batched_ex_{tag}", n, *ops, 1.0, *ptrs, _arr(X, dtype, size, "X"), 0.0,
+          _arr(Y, dtype, size, "Y"), batch, cols.data_ptr(), cols.numel() * cols.element_size(), _stream(None))
+    return cols
 
 
 def kron2d_backward_f32(n, A, B, X, dY, dX, dA, dB, batch, ws=None, stream=None):
@@ -479,7 +510,7 @@ def _nd_call(tag, m, n, ops, alpha, factors, ldf, ldfp, X, beta, Y, batch, ws, s
             raise ValueError(f"factor {k}: leading dimension or operand stride too small")
         one = rows[k] + ldf[k] * (cols[k] - 1)
         need = one + (batch - 1) * ldfp[k] if batch > 0 else one
-        ptrs.append(_arr(factors[k], dtype, need, f"factor {k}").value)
+        ptrs.append(_arr(factors[k], dtype, need, f"factor {k}"))
     nx, ny = batch * int(np.prod(n)), batch * int(np.prod(m))
     px = _arr(X, dtype, nx, "X")
     py = _arr(Y, dtype, ny, "Y")
@@ -775,6 +806,11 @@ def _groups_array(groups):
     return arr, len(groups)
 
 
+# kron_group_grad_t: dim, n, mode, reserved, the nine pointers, count
+_GRAD_STRUCT = struct.Struct("=4i9Qq")
+assert _GRAD_STRUCT.size == ctypes.sizeof(KronGroupGrad)
+
+
 def _grad_groups_array(groups):
     """groups: iterable of dicts with dim, n, A, B, (C), X, dY, count, the
     optional outputs dX, dA, dB, (dC) and an optional mode (MODE_F32 default
@@ -789,23 +825,23 @@ def _grad_groups_array(groups):
         if mode not in (MODE_F32, MODE_F64):
             raise ValueError(f"group {i}: mode must be MODE_F32 or MODE_F64")
         dt = _MODE_DTYPE[mode]
-        size = count * n ** dim
-        names = ("A", "B", "C")[:dim]
-        mats = [_arr(g[k], dt, n * n, f"group {i} {k}") for k in names]
-        want = [g.get(k) for k in ("dA", "dB", "dC")[:dim]]
-        outs = [_arr(t, dt, n * n, f"group {i} d{k}") if t is not None else None for t, k in zip(want, names)]
-        px = _arr(g["X"], dt, size, f"group {i} X") if g.get("X") is not None else None
-        if px is None and any(t is not None for t in want) and count > 0:
+        nn, size = n * n, count * n ** dim
+        three, get = dim == 3, g.get
+        X, dY, dX = get("X"), g["dY"], get("dX")
+        try:
+            # one address per tensor, 0 for an output that is not asked for
+            pa, pb = _arr(g["A"], dt, nn, "A") or 0, _arr(g["B"], dt, nn, "B") or 0
+            pc = (_arr(g["C"], dt, nn, "C") or 0) if three else 0
+            ga, gb = _arr(get("dA"), dt, nn, "dA") or 0, _arr(get("dB"), dt, nn, "dB") or 0
+            gc = (_arr(get("dC"), dt, nn, "dC") or 0) if three else 0
+            px, pdy, pdx = _arr(X, dt, size, "X") or 0, _arr(dY, dt, size, "dY") or 0, _arr(dX, dt, size, "dX") or 0
+        except (TypeError, ValueError) as e:
+            raise type(e)(f"group {i} {e}") from None
+        if X is None and count > 0 and any(get(k) is not None for k in ("dA", "dB", "dC")[:dim]):
             raise ValueError(f"group {i}: X is needed for factor gradients")
-        pdy = _arr(g["dY"], dt, size, f"group {i} dY")
-        pdx = None
-        if g.get("dX") is not None:
-            pdx = _arr(g["dX"], dt, size, f"group {i} dX")
-            for other in ("X", "dY"):
-                if g.get(other) is not None and size > 0 and g["dX"].data_ptr() == g[other].data_ptr():
-                    raise ValueError(f"group {i}: dX must not alias {other}")
-        arr[i] = KronGroupGrad(dim, n, mode, 0, mats[0], mats[1], mats[2] if dim == 3 else None, px, pdy, pdx,
-                               outs[0], outs[1], outs[2] if dim == 3 else None, count)
+        if dX is not None and size > 0 and (pdx == px or pdx == pdy):
+            raise ValueError(f"group {i}: dX must not alias {'X' if pdx == px else 'dY'}")
+        _GRAD_STRUCT.pack_into(arr, i * _GRAD_STRUCT.size, dim, n, mode, 0, pa, pb, pc, px, pdy, pdx, ga, gb, gc, count)
     return arr, len(groups)
 
 

@@ -9,8 +9,9 @@ and the factors are ordinary (row-major) n x n tensors, so that
 i.e. factor m acts along operand axis m.  On the memory-order vector this is
 vec(Y_p) = (A kron B (kron C)) vec(X_p), the library's C ABI convention; for
 2-D it is the paper's Y_p = B X_p A^T on the column-major view of X_p.  The
-wrapper gives the kernels the column-major copies of the n x n factors (the
-paper's transpose-once, Section 2.2); all batch work runs in libkron.
+wrapper has the library prepare the column-major copies of the n x n factors
+(the paper's transpose-once, Section 2.2) in the launch before the action and
+keeps them for the backward; all batch work runs in libkron.
 Backward: dX from the transposed action, dA/dB/dC batch-reduced by the
 factor-gradient kernels (deterministic).  The backward is first order only:
 its kernels write plain tensors with no graph, so asking for a second
@@ -20,14 +21,8 @@ import torch
 
 from . import _binding as kb
 
-_FWD = {
-    (2, torch.float32, "f32"): kb.kron2d_batched_f32,
-    (3, torch.float32, "f32"): kb.kron3d_batched_f32,
-    (2, torch.float64, "f64"): kb.kron2d_batched_f64,
-    (3, torch.float64, "f64"): kb.kron3d_batched_f64,
-    (2, torch.float32, "bf16x3"): kb.kron2d_batched_f32_bf16x3,
-    (3, torch.float32, "bf16x3"): kb.kron3d_batched_f32_bf16x3,
-}
+_MODES = {torch.float32: ("f32", "bf16x3"), torch.float64: ("f64",)}
+_SPLIT = {2: kb.kron2d_batched_f32_bf16x3, 3: kb.kron3d_batched_f32_bf16x3}
 _BWD = {
     (2, torch.float32): (kb.kron2d_backward_f32, kb.MODE_F32),
     (3, torch.float32): (kb.kron3d_backward_f32, kb.MODE_F32),
@@ -36,8 +31,9 @@ _BWD = {
 }
 
 
-def _colmajor(M):
-    return M.detach().t().contiguous()
+def _each(cm, dim, n):
+    """The column-major factors of their one array."""
+    return cm.view(dim, n * n).unbind(0)
 
 
 def _check(X, mats):
@@ -61,19 +57,23 @@ class KronFn(torch.autograd.Function):
     @staticmethod
     def forward(ctx, mode, X, *mats):
         dim, n = _check(X, mats)
+        if mode not in _MODES.get(X.dtype, ()):
+            raise KeyError((dim, X.dtype, mode))
         X = X.contiguous()
-        cm = [_colmajor(M) for M in mats]
         Y = torch.empty_like(X)
-        fn = _FWD[(dim, X.dtype, mode)]
-        fn(n, *cm, X, Y, X.shape[0])
-        ctx.save_for_backward(X, *cm)
+        if mode == "bf16x3":
+            cm = torch.stack([M.detach().t() for M in mats]).view(-1)
+            _SPLIT[dim](n, *_each(cm, dim, n), X, Y, X.shape[0])
+        else:
+            cm = kb.forward_rows(dim, n, mats, X, Y, X.shape[0])
+        ctx.save_for_backward(X, cm)
         ctx.dim, ctx.n = dim, n
         return Y
 
     @staticmethod
     @torch.autograd.function.once_differentiable
     def backward(ctx, dY):
-        X, *cm = ctx.saved_tensors
+        X, cm = ctx.saved_tensors
         dim, n = ctx.dim, ctx.n
         batch = X.shape[0]
         dY = dY.contiguous()
@@ -86,7 +86,7 @@ class KronFn(torch.autograd.Function):
             ws = torch.empty(max(1, kb.kron_backward_workspace_size(dim, n, batch, mode)), dtype=torch.uint8,
                              device=X.device)
         if dX is not None or ws is not None:
-            fn(n, *cm, X, dY, dX, *grads, batch, ws)
+            fn(n, *_each(cm, dim, n), X, dY, dX, *grads, batch, ws)
         # the kernels return column-major n x n gradients; view them as torch matrices
         gm = [g.view(n, n).t() if g is not None else None for g in grads]
         return (None, dX, *gm)
