@@ -19,9 +19,13 @@
 // Three LDS images (X, D and a work image) suffice, because X1 and D1 wait in
 // registers while the work image holds D2.
 //
-// A contraction takes four columns per 16x16x4 instruction: lane (L, g) reads
-// element L of column g of both images.  Its rows and columns beyond n hold
-// values that no result uses, so only missing columns are masked.
+// A contraction from n = 9 on takes four columns per 16x16x4 instruction: lane
+// (L, g) reads element L of column g of both images.  Its rows and columns
+// beyond n hold values that no result uses, so only missing columns are masked.
+// Up to n = 4 and 8 that wastes most of the products (n^2 / 256 of them count),
+// and the smaller forms below take their place: with every gradient and dX at
+// 128 MiB of X, FP32 3-D n = 2 took 679 us a training step and now takes 150,
+// FP32 3-D n = 5 229 us a backward and now 144, FP64 3-D n = 5 204 and now 99.
 #pragma once
 
 #include "kron_cols.hpp"
@@ -29,8 +33,12 @@
 namespace kron {
 
 // Operands per tile, wavefronts per workgroup, and wavefronts per SIMD the
-// registers are held to; measured at 512 MiB of X.  FP32 3-D n = 16: three
-// workgroups of four wavefronts fit a CU (408 us; two of eight: 430).
+// registers are held to.  At 512 MiB of X, FP32 3-D n = 16: three workgroups of
+// four wavefronts fit a CU (408 us; two of eight: 430).  At 128 MiB: FP32 3-D
+// n = 5 to 8 at 3 a SIMD, because at 5 the sums spill (n = 8: 101 against
+// 333 us); FP64 2-D at 3 a SIMD on tiles that let three or more workgroups
+// share a CU (n = 8: 185 to 90 us, n = 12: 148 to 111, n = 16: 176 to 99).
+// Twice and four times the operands for n <= 4: up to three times slower.
 struct BwdShape {
   int ops, waves, per_simd;
 };
@@ -43,9 +51,9 @@ constexpr BwdShape bwd_shape() {
   constexpr int v3[17] = {0, 4, 4, 4, 4, 4, 4, 4, 4, 4, 4, 4, 5, 6, 7, 8, 8};
   if (Dim == 3) {
     if (sizeof(T) == 8) return BwdShape{d3[N], v3[N], 2};
-    return BwdShape{f3[N], w3[N], N <= 8 ? 5 : N <= 12 ? 4 : 3};
+    return BwdShape{f3[N], w3[N], N <= 4 ? 5 : N <= 8 ? 3 : N <= 12 ? 4 : 3};
   }
-  if (sizeof(T) == 8) return BwdShape{N <= 8 ? 256 / N : 128 / N, 4, 2};
+  if (sizeof(T) == 8) return BwdShape{N <= 4 ? 256 / N : N <= 8 || N > 12 ? 128 / N : 64 / N, N <= 4 || N > 8 ? 4 : 2, 3};
   return BwdShape{N < 16 ? 256 / N : 8, 4, N >= 12 && N < 16 ? 3 : 4};
 }
 
@@ -72,7 +80,11 @@ struct Bwd {
   static constexpr int kMinWaves = bwd_shape<Dim, N, T>().per_simd;
   static constexpr int PL = N == 16 ? 276 : N * N + (N == 8 ? 8 : N == 4 || N == 12 ? 4 : 0);
   static constexpr int kImage = NP * PL;
-  __device__ static constexpr int swz(int row) { return N == 16 ? 4 * (row >> 2) : 0; }
+  // FP64 n = 4 and 8: row b holds element c at (c ^ b); the reads of a row per
+  // lane met 16 of the 64 banks otherwise (2-D n = 8 at 128 MiB: 255 us).
+  __device__ static constexpr int swz(int row) {
+    return N == 16 ? 4 * (row >> 2) : sizeof(T) == 8 && (N == 4 || N == 8) ? row : 0;
+  }
   __device__ static constexpr int at(int plane, int row, int col) { return plane * PL + row * N + (col ^ swz(row)); }
 };
 
@@ -82,6 +94,22 @@ struct BwdTiles {
   static constexpr int N = S::N, P = S::P, NC = S::NC, kE = S::kE, kd = S::kd, PL = S::PL, kT = S::kThreads;
   using acc_t = std::conditional_t<sizeof(T) == 8, f64x4, f32x4>;
   typedef T regs_t[NC][kE];
+  // n <= 4: a lane sums the outer products of its own columns, n * n sums a
+  // gradient; a 16x16x4 instruction would use n^3 / 1024 of its products.
+  static constexpr bool kOwn = N <= 4;
+  struct own_t {
+    T v[N * N];
+  };
+  // n = 5 to 8: 4x4x1 (FP64: 4x4x4) instructions, 16 columns each, two by two
+  // for the entries, where a 16x16x4 takes four columns of at most half its
+  // rows.  Lane i of a column holds elements 2i and 2i + 1; v[ti][tj] holds
+  // entries (2r + ti, 2j + tj), j being the lane mod 4 and r the register
+  // (FP64: the lane over 16), for the column groups of the other lane bits.
+  static constexpr bool kQuad = N > 4 && N <= 8;
+  struct quad_t {
+    std::conditional_t<sizeof(T) == 8, T, f32x4> v[2][2];
+  };
+  using sum_t = std::conditional_t<kOwn, own_t, std::conditional_t<kQuad, quad_t, acc_t>>;
 
   const int tid, wave, k0, q0;
   int plane1[NC], fast1[NC];  // column q as (plane, position) of the middle and fast axes
@@ -105,6 +133,7 @@ struct BwdTiles {
     }
   }
 
+  __device__ __forceinline__ static int lane() { return threadIdx.x & 63; }
   __device__ __forceinline__ bool has(int s) const { return !S::kMat || N % 4 == 0 || s + 1 < kE || k0 + kd * s < N; }
 
   // LDS offset of element s of column c along an axis: 0 the fast one, 1 the
@@ -157,6 +186,49 @@ struct BwdTiles {
   // keep the matrix pipe fed, so that the running sum grows by one rounding per
   // tile instead of one per column.
   template <int kAxis>
+  __device__ __forceinline__ void contract(const T* U, const T* V, int planes, own_t& sum) const {
+    regs_t u, v;
+    get<kAxis>(U, u);
+    get<kAxis>(V, v);
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      if (ok[c] && (kAxis == 2 ? op0[c] * N : plane1[c]) < planes) {
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+          for (int j = 0; j < N; ++j) sum.v[i * N + j] += u[c][i] * v[c][j];
+      }
+  }
+  template <int kAxis>
+  __device__ __forceinline__ void contract(const T* U, const T* V, int planes, quad_t& sum) const {
+    const int i = threadIdx.x & 3, k0 = min(2 * i, N - 1), k1 = min(2 * i + 1, N - 1);
+#pragma unroll
+    for (int r = 0; r < (S::kCols + 16 * S::kWaves - 1) / (16 * S::kWaves); ++r) {
+      const int q = 16 * (S::kWaves * r + wave) + (lane() >> 2);
+      // element k of column q
+      auto at = [&](int k) {
+        if constexpr (kAxis == 0) return S::at(q / N, q % N, k);
+        else if constexpr (kAxis == 1) return S::at(q / N, k, q % N);
+        else return S::at(q / (N * N) * N + k, q / N % N, q % N);
+      };
+      T u[2] = {0, 0}, v[2] = {0, 0};
+      if (q < planes * N) {
+        u[0] = in_lds(U)[at(k0)];
+        u[1] = in_lds(U)[at(k1)];
+        v[0] = in_lds(V)[at(k0)];
+        v[1] = in_lds(V)[at(k1)];
+      }
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+          if constexpr (sizeof(T) == 8)
+            sum.v[a][b] = __builtin_amdgcn_mfma_f64_4x4x4f64(u[a], v[b], sum.v[a][b], 0, 0, 0);
+          else
+            sum.v[a][b] = __builtin_amdgcn_mfma_f32_4x4x1f32(u[a], v[b], sum.v[a][b], 0, 0, 0);
+    }
+  }
+  template <int kAxis>
   __device__ __forceinline__ void contract(const T* U, const T* V, int planes, acc_t& sum) const {
     acc_t acc[2] = {acc_t{0, 0, 0, 0}, acc_t{0, 0, 0, 0}};
     add_columns<kAxis>(U, V, planes, acc);
@@ -183,9 +255,9 @@ struct BwdTiles {
     int lane[G];
 #pragma unroll
     for (int j = 0; j < G; ++j) {
-      if constexpr (kAxis == 0) lane[j] = (4 * j + g < N ? 4 * j + g : 0) * N + (L ^ S::swz(4 * j));
-      else if constexpr (kAxis == 1) lane[j] = L * N + ((4 * j) ^ S::swz(L)) + g;
-      else lane[j] = L * PL + g;
+      if constexpr (kAxis == 0) lane[j] = (4 * j + g < N ? 4 * j + g : 0) * N + (L ^ S::swz(4 * j + g));
+      else if constexpr (kAxis == 1) lane[j] = L * N + ((4 * j + g) ^ S::swz(L));
+      else lane[j] = L * PL;
     }
     for (int r = wave; r < planes; r += S::kWaves) {
       int off, sw = 0;
@@ -199,7 +271,7 @@ struct BwdTiles {
 #pragma unroll
       for (int j = 0; j < G; ++j) {
         int e = lane[j] + off;
-        if constexpr (kAxis == 2) e += (4 * j) ^ sw;
+        if constexpr (kAxis == 2) e += (4 * j + g) ^ sw;
         T u, v;
         if (N % 4 != 0 && j == G - 1) {
           const bool in = 4 * j + g < N;
@@ -260,16 +332,15 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
   using T = typename S::io_t;
   using Tiles = BwdTiles<S>;
   constexpr int N = S::N, P = S::P, NC = S::NC, kE = S::kE, Dim = S::Dim, kWaves = S::kWaves;
-  constexpr int kRed = kWaves * Dim * 256;  // the wavefronts' sums, at the end
+  // the sums, at the end: of the wavefronts, or one factor's of the lanes
+  constexpr int kRed = Tiles::kOwn ? S::kThreads * N * N : Tiles::kQuad ? S::kThreads * 16 : kWaves * Dim * 256;
   __shared__ __attribute__((aligned(16))) T lds[3 * S::kImage > kRed ? 3 * S::kImage : kRed];
   T* const ix = lds;
   T* const id = lds + S::kImage;
   T* const iw = lds + 2 * S::kImage;
   const Tiles tl;
   const int lane = threadIdx.x & 63;
-  typename Tiles::acc_t acc[Dim];
-#pragma unroll
-  for (int f = 0; f < Dim; ++f) acc[f] = typename Tiles::acc_t{0, 0, 0, 0};
+  typename Tiles::sum_t acc[Dim] = {};
   const bool wa = which & 1, wb = which & 2, wc = which & 4;
   const typename S::template Factor<false> fA(A, lane);
   const typename S::template Factor<true> tA(A, lane), tB(B, lane);
@@ -387,20 +458,66 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
     }
   }
   if (which == 0) return;
-  // the wavefronts' partials, summed in wavefront order through LDS
-  lds_barrier();
-  const int g = lane >> 4, L = lane & 15;
+  if constexpr (Tiles::kOwn) {
+    // 16 lanes an entry: each sums every sixteenth of the lanes' sums
+    static_assert(S::kThreads >= 16 * N * N, "16 lanes an entry");
 #pragma unroll
-  for (int f = 0; f < Dim; ++f)
+    for (int f = 0; f < Dim; ++f) {
+      lds_barrier();
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      in_lds(lds)[(tl.wave * Dim + f) * 256 + (sizeof(T) == 8 ? g + 4 * r : 4 * g + r) * 16 + L] = acc[f][r];
-  lds_barrier();
-  for (int e = tl.tid; e < Dim * 256; e += S::kThreads) {
-    T sum = 0;
+      for (int e = 0; e < N * N; ++e) in_lds(lds)[e * S::kThreads + tl.tid] = acc[f].v[e];
+      lds_barrier();
+      const int e = tl.tid >> 4;
+      T sum = 0;
+      if (e < N * N) {
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) sum += in_lds(lds)[w * Dim * 256 + e];
-    ws[(int64_t)blockIdx.x * 3 * 256 + e] = sum;
+        for (int i = 0; i < S::kThreads; i += 16) sum += in_lds(lds)[e * S::kThreads + (tl.tid & 15) + i];
+      }
+#pragma unroll
+      for (int h = 8; h > 0; h >>= 1) sum += __shfl_xor(sum, h);
+      if (e < N * N && (tl.tid & 15) == 0) ws[((int64_t)blockIdx.x * 3 + f) * 256 + e / N * 16 + e % N] = sum;
+    }
+  } else if constexpr (Tiles::kQuad) {
+    // kWaves lanes an entry: each sums one wavefront's column groups
+#pragma unroll
+    for (int f = 0; f < Dim; ++f) {
+      constexpr int R = sizeof(T) == 8 ? 1 : 4;  // registers a tile of entries
+      lds_barrier();
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          T* const to = lds + (v * R + r) * S::kThreads + tl.tid;
+          if constexpr (R == 1) *in_lds(to) = acc[f].v[v >> 1][v & 1];
+          else *in_lds(to) = acc[f].v[v >> 1][v & 1][r];
+        }
+      lds_barrier();
+      const int w = tl.tid % kWaves, e = tl.tid / kWaves, tile = e >> 4, i = e >> 2 & 3, j = e & 3;
+      const T* const from = lds + (R == 1 ? tile * S::kThreads + 16 * i : (4 * tile + i) * S::kThreads) + 64 * w + j;
+      T sum = 0;
+#pragma unroll
+      for (int b = 0; b < 4 * R; ++b) sum += in_lds(from)[4 * b];
+#pragma unroll
+      for (int h = 1; h < kWaves; h <<= 1) sum += __shfl_xor(sum, h);
+      const int row = 2 * i + (tile >> 1), col = 2 * j + (tile & 1);
+      if (w == 0) ws[((int64_t)blockIdx.x * 3 + f) * 256 + row * 16 + col] = sum;
+    }
+  } else {
+    // the wavefronts' partials, summed in wavefront order through LDS
+    lds_barrier();
+    const int g = lane >> 4, L = lane & 15;
+#pragma unroll
+    for (int f = 0; f < Dim; ++f)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        in_lds(lds)[(tl.wave * Dim + f) * 256 + (sizeof(T) == 8 ? g + 4 * r : 4 * g + r) * 16 + L] = acc[f][r];
+    lds_barrier();
+    for (int e = tl.tid; e < Dim * 256; e += S::kThreads) {
+      T sum = 0;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) sum += in_lds(lds)[w * Dim * 256 + e];
+      ws[(int64_t)blockIdx.x * 3 * 256 + e] = sum;
+    }
   }
 }
 

@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("prec", ["f32", "f64"])
-@pytest.mark.parametrize("dim,n", [(2, 1), (2, 5), (2, 13), (2, 16), (3, 2), (3, 8), (3, 11), (3, 16)])
+@pytest.mark.parametrize("dim,n", [(2, 1), (2, 4), (2, 5), (2, 8), (2, 13), (2, 16), (3, 2), (3, 3), (3, 5), (3, 8), (3, 11),
+                                   (3, 16)])
 def test_backward_output_subsets(prec, dim, n):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
