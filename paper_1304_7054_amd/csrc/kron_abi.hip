@@ -387,7 +387,7 @@ int kron2d_backward_f32(int n, const float* A, const float* B, const float* X, c
   if (!B) return -3;
   if (int rc = check_backward<float>(2, n, X, dY, dX, dA, dB, nullptr, batch, ws, ws_bytes, 4)) return rc;
   if (dA || dB)
-    return finish_launch(kron::backward(2, n, A, B, nullptr, X, dY, dX, dA, dB, nullptr, batch, ws, stream));
+    return finish_launch(kron::backward({2, n, KRON_MODE_F32, 0, A, B, nullptr, X, dY, dX, dA, dB, nullptr, batch}, ws, stream));
   if (dX && batch > 0) return finish_launch(kron::fwd2d_f32(n, A, B, dY, dX, batch, stream, true));
   return 0;
 }
@@ -401,7 +401,7 @@ int kron3d_backward_f32(int n, const float* A, const float* B, const float* C, c
   if (!C) return -4;
   if (int rc = check_backward<float>(3, n, X, dY, dX, dA, dB, dC, batch, ws, ws_bytes, 5)) return rc;
   if (dA || dB || dC)
-    return finish_launch(kron::backward(3, n, A, B, C, X, dY, dX, dA, dB, dC, batch, ws, stream));
+    return finish_launch(kron::backward({3, n, KRON_MODE_F32, 0, A, B, C, X, dY, dX, dA, dB, dC, batch}, ws, stream));
   if (dX && batch > 0) return finish_launch(kron::fwd3d_f32(n, A, B, C, dY, dX, batch, stream, true));
   return 0;
 }
@@ -413,7 +413,7 @@ int kron2d_backward_f64(int n, const double* A, const double* B, const double* X
   if (!B) return -3;
   if (int rc = check_backward<double>(2, n, X, dY, dX, dA, dB, nullptr, batch, ws, ws_bytes, 4)) return rc;
   if (dA || dB)
-    return finish_launch(kron::backward(2, n, A, B, nullptr, X, dY, dX, dA, dB, nullptr, batch, ws, stream));
+    return finish_launch(kron::backward({2, n, KRON_MODE_F64, 0, A, B, nullptr, X, dY, dX, dA, dB, nullptr, batch}, ws, stream));
   if (dX && batch > 0) return finish_launch(kron::fwd2d_f64(n, A, B, dY, dX, batch, stream, true));
   return 0;
 }
@@ -427,7 +427,7 @@ int kron3d_backward_f64(int n, const double* A, const double* B, const double* C
   if (!C) return -4;
   if (int rc = check_backward<double>(3, n, X, dY, dX, dA, dB, dC, batch, ws, ws_bytes, 5)) return rc;
   if (dA || dB || dC)
-    return finish_launch(kron::backward(3, n, A, B, C, X, dY, dX, dA, dB, dC, batch, ws, stream));
+    return finish_launch(kron::backward({3, n, KRON_MODE_F64, 0, A, B, C, X, dY, dX, dA, dB, dC, batch}, ws, stream));
   if (dX && batch > 0) return finish_launch(kron::fwd3d_f64(n, A, B, C, dY, dX, batch, stream, true));
   return 0;
 }
@@ -470,9 +470,9 @@ size_t kron_grouped_backward_workspace_size(const kron_group_grad_t* groups, int
 
 namespace {
 
-// Streams the grouped backward spreads its groups over (per device, created
-// on first use, default priority, never destroyed): one group's kernels are
-// too small to fill the GPU on their own.
+// Streams a grouped backward spreads groups without factor gradients over (per
+// device, created on first use, default priority, never destroyed): one such
+// group's kernel is too small to fill the GPU on its own.
 constexpr int kBwdStreams = 8;
 std::mutex g_bwd_mu;
 hipStream_t g_bwd_streams[64][kBwdStreams];
@@ -494,21 +494,68 @@ const hipStream_t* bwd_streams() {
   return g_bwd_streams[dev];
 }
 
-int grad_group_run(const kron_group_grad_t& d, void* w, size_t b, hipStream_t stream) {
+// dX alone: the adjoint action of dY.
+int grad_group_dx(const kron_group_grad_t& d, hipStream_t s) {
   if (d.mode == KRON_MODE_F32) {
     using T = float;
-    if (d.dim == 2)
-      return kron2d_backward_f32(d.n, (const T*)d.A, (const T*)d.B, (const T*)d.X, (const T*)d.dY, (T*)d.dX,
-                                 (T*)d.dA, (T*)d.dB, d.count, w, b, stream);
-    return kron3d_backward_f32(d.n, (const T*)d.A, (const T*)d.B, (const T*)d.C, (const T*)d.X, (const T*)d.dY,
-                               (T*)d.dX, (T*)d.dA, (T*)d.dB, (T*)d.dC, d.count, w, b, stream);
+    if (d.dim == 2) return kron::fwd2d_f32(d.n, (const T*)d.A, (const T*)d.B, (const T*)d.dY, (T*)d.dX, d.count, s, true);
+    return kron::fwd3d_f32(d.n, (const T*)d.A, (const T*)d.B, (const T*)d.C, (const T*)d.dY, (T*)d.dX, d.count, s, true);
   }
   using T = double;
-  if (d.dim == 2)
-    return kron2d_backward_f64(d.n, (const T*)d.A, (const T*)d.B, (const T*)d.X, (const T*)d.dY, (T*)d.dX,
-                               (T*)d.dA, (T*)d.dB, d.count, w, b, stream);
-  return kron3d_backward_f64(d.n, (const T*)d.A, (const T*)d.B, (const T*)d.C, (const T*)d.X, (const T*)d.dY,
-                             (T*)d.dX, (T*)d.dA, (T*)d.dB, (T*)d.dC, d.count, w, b, stream);
+  if (d.dim == 2) return kron::fwd2d_f64(d.n, (const T*)d.A, (const T*)d.B, (const T*)d.dY, (T*)d.dX, d.count, s, true);
+  return kron::fwd3d_f64(d.n, (const T*)d.A, (const T*)d.B, (const T*)d.C, (const T*)d.dY, (T*)d.dX, d.count, s, true);
+}
+
+// The dX-only groups.  Fork: the worker streams wait for the work already on
+// `stream`; the groups go to them, largest first, each to the stream with the
+// least work so far (elements read and written, plus a fixed cost for the
+// launch); join: `stream` waits for every worker.  Without worker streams (or
+// with one group) they run on `stream` in descriptor order.
+int grad_groups_dx(std::vector<const kron_group_grad_t*>& groups, hipStream_t stream) {
+  const hipStream_t* workers = groups.size() > 1 ? bwd_streams() : nullptr;
+  hipEvent_t fork = nullptr;
+  if (workers) {
+    if (hipEventCreateWithFlags(&fork, hipEventDisableTiming) != hipSuccess) {
+      workers = nullptr;
+    } else {
+      hipError_t e = hipEventRecord(fork, stream);
+      for (int w = 0; w < kBwdStreams && e == hipSuccess; ++w) e = hipStreamWaitEvent(workers[w], fork, 0);
+      if (e != hipSuccess) {
+        (void)hipEventDestroy(fork);
+        return (int)e;
+      }
+    }
+  }
+  auto cost = [](const kron_group_grad_t* d) {
+    return 3.0 * (double)d->count * (d->dim == 3 ? (double)d->n * d->n * d->n : (double)d->n * d->n) + 2.0e5;
+  };
+  if (workers)
+    std::stable_sort(groups.begin(), groups.end(), [&](auto* a, auto* b) { return cost(a) > cost(b); });
+  double load[kBwdStreams] = {};
+  int rc = 0;
+  for (const kron_group_grad_t* d : groups) {
+    hipStream_t s = stream;
+    if (workers) {
+      const int w = (int)(std::min_element(load, load + kBwdStreams) - load);
+      load[w] += cost(d);
+      s = workers[w];
+    }
+    // descriptors were checked, so only a launch failure can end the loop
+    rc = finish_launch(grad_group_dx(*d, s));
+    if (rc != 0) break;
+  }
+  if (workers) {
+    for (int w = 0; w < kBwdStreams; ++w) {
+      hipEvent_t done = nullptr;
+      hipError_t e = hipEventCreateWithFlags(&done, hipEventDisableTiming);
+      if (e == hipSuccess) e = hipEventRecord(done, workers[w]);
+      if (e == hipSuccess) e = hipStreamWaitEvent(stream, done, 0);
+      if (done) (void)hipEventDestroy(done);
+      if (e != hipSuccess && rc == 0) rc = (int)e;
+    }
+    (void)hipEventDestroy(fork);
+  }
+  return rc;
 }
 
 }  // namespace
@@ -524,77 +571,24 @@ int kron_grouped_backward(const kron_group_grad_t* groups, int ngroups, void* ws
   }
   if (need > 0 && !ws) return -3;
   if (ws_bytes < need) return -4;
-  // Fork: the worker streams wait for the work already on `stream`; the
-  // groups go to them in turn; join: `stream` waits for every worker.  Each
-  // group's kernels stay in order on one stream, and its result does not
-  // depend on what runs beside it.  Without worker streams (or with one
-  // group) the groups run on `stream` in descriptor order.
-  const hipStream_t* workers = ngroups > 1 ? bwd_streams() : nullptr;
-  hipEvent_t fork = nullptr;
-  if (workers) {
-    if (hipEventCreateWithFlags(&fork, hipEventDisableTiming) != hipSuccess) {
-      workers = nullptr;
-    } else {
-      hipError_t e = hipEventRecord(fork, stream);
-      for (int w = 0; w < kBwdStreams && e == hipSuccess; ++w) e = hipStreamWaitEvent(workers[w], fork, 0);
-      if (e != hipSuccess) {
-        (void)hipEventDestroy(fork);
-        return (int)e;
-      }
-    }
-  }
-  // Each group's workspace slice, in descriptor order.
-  std::vector<size_t> off(ngroups);
-  {
-    size_t o = 0;
-    for (int i = 0; i < ngroups; ++i) {
-      off[i] = o;
-      o += grad_group_bytes(groups[i]);
-    }
-  }
-  // Largest groups first, each to the stream with the least work so far
-  // (elements read and written, plus a fixed cost per group for its launches).
-  std::vector<int> order(ngroups);
-  std::vector<double> cost(ngroups);
+  // The groups with factor gradients share launches; each has its workspace
+  // slice, in descriptor order.
+  std::vector<std::pair<const kron_group_grad_t*, void*>> full;
+  std::vector<const kron_group_grad_t*> dx;
+  uint8_t* slice = static_cast<uint8_t*>(ws);
   for (int i = 0; i < ngroups; ++i) {
     const kron_group_grad_t& d = groups[i];
-    const double e = (double)d.count * (d.dim == 3 ? (double)d.n * d.n * d.n : (double)d.n * d.n);
-    cost[i] = 3.0 * e + 2.0e5;
-    order[i] = i;
-  }
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
-  double load[kBwdStreams] = {};
-  uint8_t* base = static_cast<uint8_t*>(ws);
-  int rc = 0;
-  for (int k = 0; k < ngroups && rc == 0; ++k) {
-    const int i = order[k];
-    const kron_group_grad_t& d = groups[i];
     const size_t b = grad_group_bytes(d);
-    hipStream_t s = stream;
-    if (workers) {
-      int w = 0;
-      for (int j = 1; j < kBwdStreams; ++j)
-        if (load[j] < load[w]) w = j;
-      load[w] += cost[i];
-      s = workers[w];
-    }
-    // descriptors were checked above, so only a launch failure can end the loop
-    rc = grad_group_run(d, b ? base + off[i] : nullptr, b, s);
+    if (d.dA || d.dB || (d.dim == 3 && d.dC)) full.emplace_back(&d, slice);
+    else if (d.dX && d.count > 0) dx.push_back(&d);
+    slice += b;
   }
-  if (workers) {
-    for (int w = 0; w < kBwdStreams; ++w) {
-      hipEvent_t done = nullptr;
-      hipError_t e = hipEventCreateWithFlags(&done, hipEventDisableTiming);
-      if (e == hipSuccess) e = hipEventRecord(done, workers[w]);
-      if (e == hipSuccess) e = hipStreamWaitEvent(stream, done, 0);
-      if (done) (void)hipEventDestroy(done);
-      if (e != hipSuccess && rc == 0) rc = (int)e;
-    }
-    (void)hipEventDestroy(fork);
+  if (!full.empty()) {
+    kron::backward_grouped(full, stream);
+    if (int rc = finish_launch(0)) return rc > 0 ? rc : -1;
   }
-  if (rc > 0) return rc;
-  if (rc < 0) return -1;
-  return 0;
+  const int rc = dx.empty() ? 0 : grad_groups_dx(dx, stream);
+  return rc < 0 ? -1 : rc;
 }
 
 size_t kron_grouped_workspace_size(const kron_group_t* groups, int ngroups) {

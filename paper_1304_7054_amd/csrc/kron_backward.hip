@@ -1,4 +1,8 @@
 // Launch of the backward kernels (FP32 and FP64).
+#include <algorithm>
+#include <utility>
+#include <vector>
+
 #include "kron.h"
 #include "kron_backward.hpp"
 #include "kron_launch.hpp"
@@ -23,51 +27,130 @@ size_t grad_workspace_bytes(int dim, int n, int64_t batch, int elem_bytes) {
 
 namespace {
 
-// The workgroup count is a fixed function of the batch and the device, so the
-// summation order (and the result) is the same on every call.
+// Workgroups of a group's tiles.  A fixed function of the batch and the
+// device, so the summation order (and the result) is the same on every call.
 template <typename T, int Dim, int N>
-void launch_backward(const T* A, const T* B, const T* C, const T* X, const T* dY, T* dX, T* dA, T* dB, T* dC,
-                     int64_t batch, void* ws, hipStream_t stream) {
+unsigned backward_blocks(int64_t batch) {
   using S = Bwd<T, Dim, N>;
-  const int which = (dA ? 1 : 0) | (dB ? 2 : 0) | (dC ? 4 : 0);
-  T* part = static_cast<T*>(ws);
-  int64_t nblocks = 0;
-  if (batch > 0) {
-    auto k = kron_backward_kernel<S>;
-    const int64_t tiles = (batch + S::P - 1) / S::P;
-    const int64_t cap = std::min((int64_t)device_cus() * occupancy_blocks(k, S::kThreads), grad_waves(Dim, N, batch));
-    nblocks = std::min(tiles, cap);
-    hipLaunchKernelGGL(k, dim3((unsigned)nblocks), dim3(S::kThreads), 0, stream, A, B, C, X, dY, dX, part, batch, tiles,
-                       which);
-  }
-  hipLaunchKernelGGL((kron_backward_sum_kernel<T, N>), dim3(Dim * N * N), dim3(256), 0, stream, part, nblocks, dA, dB,
-                     dC);
+  const int64_t tiles = (batch + S::P - 1) / S::P;
+  const int64_t cap = std::min((int64_t)device_cus() * occupancy_blocks(kron_backward_kernel<S>, S::kThreads),
+                               grad_waves(Dim, N, batch));
+  return (unsigned)std::min(tiles, cap);
 }
 
-template <typename T, int Dim>
-int backward_n(int n, const T* A, const T* B, const T* C, const T* X, const T* dY, T* dX, T* dA, T* dB, T* dC,
-               int64_t batch, void* ws, hipStream_t s) {
-  int rc = -1;
+template <typename T>
+BwdGroup group_of(const kron_group_grad_t& d, void* ws) {
+  BwdGroup g{};
+  g.A = d.A, g.B = d.B, g.C = d.C, g.X = d.X, g.dY = d.dY, g.dX = d.dX, g.ws = ws;
+  g.out[0] = d.dA, g.out[1] = d.dB, g.out[2] = d.dim == 3 ? d.dC : nullptr;
+  for (int f = 0; f < 3; ++f) g.which |= g.out[f] ? 1 << f : 0;
+  g.batch = d.count;
+  g.n = d.n;
+  g.rows = (unsigned)(d.dim * d.n);
   static_for<KRON_MAX_N>([&](auto i) {
     constexpr int N = decltype(i)::value + 1;
-    if (n != N) return;
-    launch_backward<T, Dim, N>(A, B, C, X, dY, dX, dA, dB, dC, batch, ws, s);
-    rc = 0;
+    if (d.n == N) g.blocks = d.dim == 2 ? backward_blocks<T, 2, N>(d.count) : backward_blocks<T, 3, N>(d.count);
   });
-  return rc;
+  return g;
+}
+
+template <typename T, int K>
+void launch_sum(BwdTable<K>& tab, hipStream_t stream) {
+  unsigned rows = 0;
+  for (int i = 0; i < tab.count; ++i) {
+    tab.g[i].row = rows;
+    rows += tab.g[i].rows;
+  }
+  hipLaunchKernelGGL((kron_backward_sum_kernel<T, K>), dim3(rows), dim3(1024), 0, stream, tab);
+}
+
+template <typename T, int Dim, int kClass>
+void launch_class(const BwdTable<kBwdGroups>& tab, unsigned blocks, hipStream_t stream) {
+  hipLaunchKernelGGL((kron_backward_grouped_kernel<T, Dim, kClass>), dim3(blocks),
+                     dim3(BwdClass<T, Dim, kClass>().threads), 0, stream, tab);
+}
+
+template <typename T>
+int run_one(const BwdGroup& g, int dim, hipStream_t stream) {
+  static_for<KRON_MAX_N>([&](auto i) {
+    constexpr int N = decltype(i)::value + 1;
+    if (g.n != N || g.blocks == 0) return;
+    auto go = [&](auto k, int threads) {
+      hipLaunchKernelGGL(k, dim3(g.blocks), dim3(threads), 0, stream, (const T*)g.A, (const T*)g.B, (const T*)g.C,
+                         (const T*)g.X, (const T*)g.dY, (T*)g.dX, (T*)g.ws, g.batch, g.which);
+    };
+    if (dim == 2) go(kron_backward_kernel<Bwd<T, 2, N>>, Bwd<T, 2, N>::kThreads);
+    else go(kron_backward_kernel<Bwd<T, 3, N>>, Bwd<T, 3, N>::kThreads);
+  });
+  BwdTable<1> tab;
+  tab.count = 1;
+  tab.g[0] = g;
+  launch_sum<T>(tab, stream);
+  return 0;
+}
+
+template <typename T>
+void run_groups(std::vector<std::pair<const kron_group_grad_t*, void*>>& groups, hipStream_t stream) {
+  // the groups with the longest workgroups first, so that short ones end a launch
+  std::vector<BwdGroup> all;
+  std::vector<int> dims, order;
+  std::vector<double> cost;
+  for (auto& [d, ws] : groups) {
+    all.push_back(group_of<T>(*d, ws));
+    dims.push_back(d->dim);
+    order.push_back((int)order.size());
+    double e = (double)d->count / std::max(1u, all.back().blocks);
+    for (int k = 0; k < d->dim; ++k) e *= d->n;
+    cost.push_back(e);
+  }
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
+  for (int dim = 3; dim >= 2; --dim)
+    static_for<kBwdClasses>([&](auto c) {
+      constexpr int kClass = kBwdClasses - 1 - decltype(c)::value;
+      BwdTable<kBwdGroups> tab;
+      tab.count = 0;
+      unsigned blocks = 0;
+      auto flush = [&] {
+        if (tab.count == 0) return;
+        if (dim == 2) launch_class<T, 2, kClass>(tab, blocks, stream);
+        else launch_class<T, 3, kClass>(tab, blocks, stream);
+        tab.count = 0;
+        blocks = 0;
+      };
+      for (int i : order) {
+        if (dims[i] != dim || all[i].blocks == 0) continue;
+        if ((dim == 2 ? bwd_class<T, 2>(all[i].n) : bwd_class<T, 3>(all[i].n)) != kClass) continue;
+        tab.g[tab.count] = all[i];
+        tab.g[tab.count++].first = blocks;
+        blocks += all[i].blocks;
+        if (tab.count == kBwdGroups) flush();
+      }
+      flush();
+    });
+  for (size_t at = 0; at < all.size(); at += kBwdGroups) {
+    BwdTable<kBwdGroups> tab;
+    tab.count = (int)std::min(all.size() - at, (size_t)kBwdGroups);
+    std::copy_n(all.begin() + at, tab.count, tab.g);
+    launch_sum<T>(tab, stream);
+  }
 }
 
 }  // namespace
 
-int backward(int dim, int n, const float* A, const float* B, const float* C, const float* X, const float* dY,
-             float* dX, float* dA, float* dB, float* dC, int64_t batch, void* ws, hipStream_t s) {
-  return dim == 2 ? backward_n<float, 2>(n, A, B, C, X, dY, dX, dA, dB, nullptr, batch, ws, s)
-                  : backward_n<float, 3>(n, A, B, C, X, dY, dX, dA, dB, dC, batch, ws, s);
+int backward(const kron_group_grad_t& d, void* ws, hipStream_t stream) {
+  return d.mode == KRON_MODE_F32 ? run_one<float>(group_of<float>(d, ws), d.dim, stream)
+                                 : run_one<double>(group_of<double>(d, ws), d.dim, stream);
 }
-int backward(int dim, int n, const double* A, const double* B, const double* C, const double* X, const double* dY,
-             double* dX, double* dA, double* dB, double* dC, int64_t batch, void* ws, hipStream_t s) {
-  return dim == 2 ? backward_n<double, 2>(n, A, B, C, X, dY, dX, dA, dB, nullptr, batch, ws, s)
-                  : backward_n<double, 3>(n, A, B, C, X, dY, dX, dA, dB, dC, batch, ws, s);
+
+void backward_grouped(const std::vector<std::pair<const kron_group_grad_t*, void*>>& groups, hipStream_t stream) {
+  for (int mode : {KRON_MODE_F32, KRON_MODE_F64}) {
+    std::vector<std::pair<const kron_group_grad_t*, void*>> mine;
+    for (auto& g : groups)
+      if (g.first->mode == mode) mine.push_back(g);
+    if (mine.empty()) continue;
+    if (mode == KRON_MODE_F32) run_groups<float>(mine, stream);
+    else run_groups<double>(mine, stream);
+  }
 }
 
 }  // namespace kron

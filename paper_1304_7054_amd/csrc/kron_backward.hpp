@@ -321,20 +321,30 @@ struct BwdTiles {
   __device__ __forceinline__ static int flat(int e) { return S::at(e / (N * N), e / N % N, e % N); }
 };
 
-// `which` bit f asks for factor f's gradient; dX may be null (then some
-// gradient is wanted).  Partials: ws[(block * 3 + f) * 256 + row * 16 + col].
+// LDS elements of a workgroup: the images, or at the end the sums of the
+// wavefronts, or one factor's of the lanes.
 template <class S>
-__global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::kMinWaves))) void kron_backward_kernel(
-    const typename S::io_t* __restrict__ A, const typename S::io_t* __restrict__ B,
+constexpr int backward_lds() {
+  using Tiles = BwdTiles<S>;
+  constexpr int kRed = Tiles::kOwn    ? S::kThreads * S::N * S::N
+                       : Tiles::kQuad ? S::kThreads * 16
+                                      : S::kWaves * S::Dim * 256;
+  return 3 * S::kImage > kRed ? 3 * S::kImage : kRed;
+}
+
+// Workgroup `block` of `nblocks`: its tiles and its partial sums.  `which` bit
+// f asks for factor f's gradient; dX may be null (then some gradient is
+// wanted).  Partials: ws[(block * 3 + f) * 256 + row * 16 + col].
+template <class S>
+__device__ __forceinline__ void backward_block(
+    typename S::io_t* const lds, const typename S::io_t* __restrict__ A, const typename S::io_t* __restrict__ B,
     const typename S::io_t* __restrict__ C, const typename S::io_t* __restrict__ X,
     const typename S::io_t* __restrict__ dY, typename S::io_t* __restrict__ dX, typename S::io_t* __restrict__ ws,
-    int64_t batch, int64_t ntiles, int which) {
+    const int64_t batch, const int which, const unsigned block, const unsigned nblocks) {
   using T = typename S::io_t;
   using Tiles = BwdTiles<S>;
   constexpr int N = S::N, P = S::P, NC = S::NC, kE = S::kE, Dim = S::Dim, kWaves = S::kWaves;
-  // the sums, at the end: of the wavefronts, or one factor's of the lanes
-  constexpr int kRed = Tiles::kOwn ? S::kThreads * N * N : Tiles::kQuad ? S::kThreads * 16 : kWaves * Dim * 256;
-  __shared__ __attribute__((aligned(16))) T lds[3 * S::kImage > kRed ? 3 * S::kImage : kRed];
+  const int64_t ntiles = (batch + P - 1) / P;
   T* const ix = lds;
   T* const id = lds + S::kImage;
   T* const iw = lds + 2 * S::kImage;
@@ -349,12 +359,12 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
     const typename S::template Factor<false> fB(B, lane);
     const typename S::template Factor<true> tC(C, lane);
     T x[NC][kE] = {}, d[NC][kE] = {}, d1[NC][kE] = {};
-    int64_t t = blockIdx.x;
+    int64_t t = block;
     if (t < ntiles) {
       if (which) tl.load_cols(X, t, batch, x);
       tl.load_cols(dY, t, batch, d);
     }
-    for (; t < ntiles; t += gridDim.x) {
+    for (; t < ntiles; t += nblocks) {
       const int64_t rem = batch - t * P;
       const int planes = (int)(rem < P ? rem : P) * N;
       lds_barrier();  // every wavefront is done with the previous tile's images
@@ -368,9 +378,9 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
         fA.template apply<NC>(x1);
       }
       lds_barrier();
-      if (t + gridDim.x < ntiles) {
-        if (which) tl.load_cols(X, t + gridDim.x, batch, x);
-        tl.load_cols(dY, t + gridDim.x, batch, d);
+      if (t + nblocks < ntiles) {
+        if (which) tl.load_cols(X, t + nblocks, batch, x);
+        tl.load_cols(dY, t + nblocks, batch, d);
       }
       tl.template get<0>(id, d1);
       tC.template apply<NC>(d1);
@@ -409,12 +419,12 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
       const int64_t rem = batch - t * P;
       return (int)(rem < P ? rem : P) * S::E;
     };
-    int64_t t = blockIdx.x;
+    int64_t t = block;
     if (t < ntiles) {
       if (which) tl.load_flat(X, t, count_of(t), x);
       tl.load_flat(dY, t, count_of(t), d);
     }
-    for (; t < ntiles; t += gridDim.x) {
+    for (; t < ntiles; t += nblocks) {
       const int count = count_of(t), planes = count / S::E;
       lds_barrier();  // every wavefront is done with the previous tile's images
 #pragma unroll
@@ -426,7 +436,7 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
         }
       }
       lds_barrier();
-      const int64_t tn = t + gridDim.x;
+      const int64_t tn = t + nblocks;
       if (tn < ntiles) {
         if (which) tl.load_flat(X, tn, count_of(tn), x);
         tl.load_flat(dY, tn, count_of(tn), d);
@@ -475,7 +485,7 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
       }
 #pragma unroll
       for (int h = 8; h > 0; h >>= 1) sum += __shfl_xor(sum, h);
-      if (e < N * N && (tl.tid & 15) == 0) ws[((int64_t)blockIdx.x * 3 + f) * 256 + e / N * 16 + e % N] = sum;
+      if (e < N * N && (tl.tid & 15) == 0) ws[((int64_t)block * 3 + f) * 256 + e / N * 16 + e % N] = sum;
     }
   } else if constexpr (Tiles::kQuad) {
     // kWaves lanes an entry: each sums one wavefront's column groups
@@ -500,7 +510,7 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
 #pragma unroll
       for (int h = 1; h < kWaves; h <<= 1) sum += __shfl_xor(sum, h);
       const int row = 2 * i + (tile >> 1), col = 2 * j + (tile & 1);
-      if (w == 0) ws[((int64_t)blockIdx.x * 3 + f) * 256 + row * 16 + col] = sum;
+      if (w == 0) ws[((int64_t)block * 3 + f) * 256 + row * 16 + col] = sum;
     }
   } else {
     // the wavefronts' partials, summed in wavefront order through LDS
@@ -516,33 +526,122 @@ __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::
       T sum = 0;
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) sum += in_lds(lds)[w * Dim * 256 + e];
-      ws[(int64_t)blockIdx.x * 3 * 256 + e] = sum;
+      ws[(int64_t)block * 3 * 256 + e] = sum;
     }
   }
 }
 
+template <class S>
+__global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(S::kMinWaves))) void kron_backward_kernel(
+    const typename S::io_t* A, const typename S::io_t* B, const typename S::io_t* C, const typename S::io_t* X,
+    const typename S::io_t* dY, typename S::io_t* dX, typename S::io_t* ws, int64_t batch, int which) {
+  __shared__ __attribute__((aligned(16))) typename S::io_t lds[backward_lds<S>()];
+  backward_block<S>(lds, A, B, C, X, dY, dX, ws, batch, which, blockIdx.x, gridDim.x);
+}
+
+// The groups of one launch, in its kernel arguments (so that a captured launch
+// keeps them).  A group's workgroups are consecutive, from `first` on.
+constexpr int kBwdGroups = 32;
+struct BwdGroup {
+  const void *A, *B, *C, *X, *dY;
+  void *dX, *ws, *out[3];
+  int64_t batch;
+  int n, which;
+  unsigned first, blocks;  // of the tile kernel
+  unsigned row, rows;      // of the sum kernel
+};
+template <int K>
+struct BwdTable {
+  int count, pad;
+  BwdGroup g[K];
+};
+static_assert(sizeof(BwdTable<kBwdGroups>) <= 4096 - 256, "kernel arguments");
+typedef const __attribute__((address_space(4))) BwdTable<kBwdGroups>* bwd_table_t;
+
+// Sizes that share a launch: those that keep as many wavefronts on a SIMD and
+// need about the same LDS, because the launch's registers and LDS are the
+// largest of its sizes.
+constexpr int kBwdClasses = 3;
+template <typename T, int Dim>
+constexpr int bwd_class(int n) {
+  if (sizeof(T) == 8) return n <= 8 ? 0 : n <= 12 ? 1 : 2;
+  if (Dim == 3) return n <= 8 ? 0 : n <= 12 ? 1 : 2;
+  return n <= 8 ? 0 : n <= 11 || n == 16 ? 1 : 2;
+}
+template <typename T, int Dim, int kClass>
+struct BwdClass {
+  int lds = 0, threads = 0, per_simd = 8;
+  constexpr BwdClass() { add(std::make_integer_sequence<int, KRON_MAX_N>{}); }
+  template <int... i>
+  constexpr void add(std::integer_sequence<int, i...>) {
+    (one<i + 1>(), ...);
+  }
+  template <int N>
+  constexpr void one() {
+    if (bwd_class<T, Dim>(N) != kClass) return;
+    using S = Bwd<T, Dim, N>;
+    if (backward_lds<S>() > lds) lds = backward_lds<S>();
+    if (S::kThreads > threads) threads = S::kThreads;
+    if (S::kMinWaves < per_simd) per_simd = S::kMinWaves;
+  }
+};
+
+// One launch over groups of one type, dimension and class.  Every group gets
+// the workgroups, tiles and sums of its own launch, hence its results.  30
+// groups (n = 2 .. 16, 2-D and 3-D, 500,000 operands, 2.1 GB): 740 us, on eight
+// streams with a launch and a sum each 878; 2,000 operands 137 us, then 442.
+template <typename T, int Dim, int kClass>
+__global__ __launch_bounds__((BwdClass<T, Dim, kClass>().threads))
+    __attribute__((amdgpu_waves_per_eu(BwdClass<T, Dim, kClass>().per_simd))) void kron_backward_grouped_kernel(
+        BwdTable<kBwdGroups>) {
+  __shared__ __attribute__((aligned(16))) T lds[BwdClass<T, Dim, kClass>().lds];
+  // the table in place: a by-value copy indexed at run time would go to scratch
+  const bwd_table_t tab = (bwd_table_t)__builtin_amdgcn_kernarg_segment_ptr();
+  int g = 0;
+  while (g + 1 < tab->count && blockIdx.x >= tab->g[g + 1].first) ++g;
+  const auto* d = &tab->g[g];
+  const int n = d->n;
+  static_for<KRON_MAX_N>([&](auto i) {
+    constexpr int N = decltype(i)::value + 1;
+    if constexpr (bwd_class<T, Dim>(N) == kClass) {
+      using S = Bwd<T, Dim, N>;
+      if (n != N || threadIdx.x >= S::kThreads) return;
+      backward_block<S>(lds, (const T*)d->A, (const T*)d->B, (const T*)d->C, (const T*)d->X, (const T*)d->dY,
+                        (T*)d->dX, (T*)d->ws, d->batch, d->which, blockIdx.x - d->first, d->blocks);
+    }
+  });
+}
+
 // dM(i, j) = sum of entry (i, j) over the partial tiles, in a fixed order in
-// FP64: one workgroup per entry of each factor, thread t sums partials t,
-// t + 256, .. and a fixed-shape tree finishes.  Column-major (i + n*j).
-template <typename T, int N>
-__global__ __launch_bounds__(256) void kron_backward_sum_kernel(const T* __restrict__ ws, int64_t nparts,
-                                                                T* __restrict__ dA, T* __restrict__ dB,
-                                                                T* __restrict__ dC) {
-  const int f = blockIdx.x / (N * N), e = blockIdx.x % (N * N);
-  T* out = f == 0 ? dA : f == 1 ? dB : dC;
+// FP64: one workgroup per row i of each factor, so that a partial is read in
+// whole rows of 16; 64 lanes share an entry, lane p sums partials p, p + 64, ..
+// and a fixed-shape tree finishes.  Column-major (i + n*j).
+template <typename T, int K>
+__global__ __launch_bounds__(1024) void kron_backward_sum_kernel(BwdTable<K>) {
+  const bwd_table_t tab = (bwd_table_t)__builtin_amdgcn_kernarg_segment_ptr();
+  int g = 0;
+  while (g + 1 < tab->count && blockIdx.x >= tab->g[g + 1].row) ++g;
+  const auto* d = &tab->g[g];
+  const int n = d->n, row = blockIdx.x - d->row, f = row / n, i = row % n;
+  T* const out = (T*)d->out[f];
   if (out == nullptr) return;
-  const int i = e % N, j = e / N;
+  const int j = threadIdx.x & 15, p = threadIdx.x >> 4;
+  const T* const ws = (const T*)d->ws + f * 256 + i * 16 + j;
+  const int64_t nparts = d->blocks;
   double s = 0.0;
-  for (int64_t w = threadIdx.x; w < nparts; w += 256) s += (double)ws[(w * 3 + f) * 256 + i * 16 + j];
-  __shared__ double red[256];
+  if (j < n) {
+#pragma unroll 8
+    for (int64_t w = p; w < nparts; w += 64) s += (double)in_global(ws)[w * 768];
+  }
+  __shared__ double red[1024];
   red[threadIdx.x] = s;
   __syncthreads();
 #pragma unroll
-  for (int h = 128; h > 0; h >>= 1) {
+  for (int h = 512; h >= 16; h >>= 1) {
     if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[e] = (T)red[0];
+  if (threadIdx.x < (unsigned)n) out[i + n * threadIdx.x] = (T)red[threadIdx.x];
 }
 
 }  // namespace kron

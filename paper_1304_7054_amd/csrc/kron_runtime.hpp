@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <utility>
+#include <vector>
 
 struct kron_group;
 
@@ -106,9 +108,8 @@ int grouped_launch(const void* ws, hipStream_t stream);
 // one pass over X and dY.  ws holds grad_workspace_bytes().
 int64_t grad_waves(int dim, int n, int64_t batch);
 size_t grad_workspace_bytes(int dim, int n, int64_t batch, int elem_bytes);
-int backward(int dim, int n, const float* A, const float* B, const float* C, const float* X, const float* dY,
-             float* dX, float* dA, float* dB, float* dC, int64_t batch, void* ws, hipStream_t s);
-int backward(int dim, int n, const double* A, const double* B, const double* C, const double* X, const double* dY,
-             double* dX, double* dA, double* dB, double* dC, int64_t batch, void* ws, hipStream_t s);
+int backward(const struct kron_group_grad& d, void* ws, hipStream_t stream);
+// The same for each of several groups (descriptor, workspace), in few launches.
+void backward_grouped(const std::vector<std::pair<const struct kron_group_grad*, void*>>& groups, hipStream_t stream);
 
 }  // namespace kron
