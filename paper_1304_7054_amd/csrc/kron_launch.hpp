@@ -71,6 +71,30 @@ void launch2d_v(int variant, const typename M::io_t* A, const typename M::io_t* 
   }
 }
 
+// Element strides of one array: s1 between columns (2-D) or along the middle
+// index (3-D), s2 along the slowest index (3-D), sp between operands.
+struct Strides {
+  int64_t s1, s2, sp;
+};
+
+// Rows that 16-byte vectors can take.
+inline bool vec_strides(const Strides& s, const void* base) {
+  return s.s1 % 4 == 0 && s.s2 % 4 == 0 && s.sp % 4 == 0 && reinterpret_cast<uintptr_t>(base) % 16 == 0;
+}
+
+// The strided action on columns in LDS (kron_strided_cols.hip) of prepared
+// factors; false, with nothing launched, where the general kernel is used:
+// operands so far apart that offsets in a tile need more than 32 bits, and
+// n = 16 with rows for 16-byte vectors, whose tiles waste nothing and equal the
+// dense kernels' results to the last bit (3-D FP32 padded by 4, 671 MB of X:
+// 413 us, columns 449; padded by 1, 128 MiB: 93, columns 56), or FP32
+// beyond 320 MiB (3-D padded by 1, 512 MiB: 337, columns 365; 256: 179, 150).
+bool strided_cols(int dim, int n, const float* A, const float* B, const float* C, const float* X, const Strides& xs,
+                  float* Y, const Strides& ys, int64_t batch, float beta, bool transx, hipStream_t stream);
+bool strided_cols(int dim, int n, const double* A, const double* B, const double* C, const double* X,
+                  const Strides& xs, double* Y, const Strides& ys, int64_t batch, double beta, bool transx,
+                  hipStream_t stream);
+
 // Modes and sizes that have a column kernel (kron_cols.hip), by measurement
 // over 1 GiB of operands (old: the best of the other variants):
 //   FP32, n < 16 (at n = 16 one operand fills a 16-slot tile, in registers):

@@ -21,12 +21,6 @@
 namespace kron {
 namespace {
 
-// Element strides of one array: s1 between columns (2-D) or along the middle
-// index (3-D), s2 along the slowest index (3-D), sp between operands.
-struct Strides {
-  int64_t s1, s2, sp;
-};
-
 // op(M) with leading dimension ld, alpha on the first factor, written dense
 // (factor f at out + f * n^2, column-major).
 template <typename T>
@@ -207,10 +201,6 @@ __global__ __launch_bounds__(kBlock) void kron_strided_kernel(const typename M::
       }
     }
   }
-}
-
-inline bool vec_strides(const Strides& s, const void* base) {
-  return s.s1 % 4 == 0 && s.s2 % 4 == 0 && s.sp % 4 == 0 && reinterpret_cast<uintptr_t>(base) % 16 == 0;
 }
 
 template <class M, int Dim, int N, bool kBeta, bool kTX>
@@ -432,9 +422,11 @@ int strided_call(int dim, int n, const char* ops, typename M::io_t alpha, const 
                      mats[1], lds[1], dim == 3 ? mats[2] : mats[1], dim == 3 ? lds[2] : lds[1], tmask, alpha, P);
   const Strides xs{ldx[0], dim == 3 ? ldx[1] : 0, ldx[dim - 1]};
   const Strides ys{ldy[0], dim == 3 ? ldy[1] : 0, ldy[dim - 1]};
-  const int rc = dim == 2 ? launch_strided<M, 2>(n, P, P + n * n, P + n * n, X, xs, Y, ys, batch, beta, transx, stream)
-                          : launch_strided<M, 3>(n, P, P + n * n, P + 2 * n * n, X, xs, Y, ys, batch, beta, false,
-                                                 stream);
+  const T *PA = P, *PB = P + n * n, *PC = P + (dim - 1) * n * n;
+  int rc = 0;
+  if (!strided_cols(dim, n, PA, PB, PC, X, xs, Y, ys, batch, beta, transx, stream))
+    rc = dim == 2 ? launch_strided<M, 2>(n, PA, PB, PC, X, xs, Y, ys, batch, beta, transx, stream)
+                  : launch_strided<M, 3>(n, PA, PB, PC, X, xs, Y, ys, batch, beta, false, stream);
   if (rc != 0) return rc;
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? 0 : (int)e;
