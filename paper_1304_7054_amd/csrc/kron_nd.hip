@@ -833,11 +833,15 @@ bool fuse_plan(int d, int k0, const int* m, const int* n, const int* opc, const 
 
 // Real 2-D and 3-D operands of equal extents up to 16, packed, with shared
 // factors: the kernels of the plain and extended entry points on factors
-// prepared in the workspace.
+// prepared in the workspace.  They scale the first factor, which alpha = 1 and
+// -1 leave exact; any other alpha belongs to the finished result, because
+// alpha * F_0 can overflow or lose bits where the result would not, and takes
+// the fused kernel (256 MiB, FP32: 3-D n = 10 93 us so and 279 there, 2-D
+// n = 16 94 and 149).
 template <typename T>
 bool nd_plain(int d, const int* m, const int* n, const int* opc, T alpha, const T* const* F, const int* ldf,
               const int64_t* ldfp, const T* X, T beta, T* Y, int64_t batch, void* ws, size_t need, hipStream_t stream) {
-  if (d != 2 && d != 3) return false;
+  if ((d != 2 && d != 3) || (alpha != T(1) && alpha != T(-1))) return false;
   const int N = n[0];
   if (N > KRON_MAX_N) return false;
   for (int k = 0; k < d; ++k)

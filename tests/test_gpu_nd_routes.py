@@ -1,0 +1,51 @@
+"""The general action on packed real cubes up to n = 16, whose products the
+plain 2-D / 3-D kernels can take, against the oracle: scales that leave the
+type's range when they meet a factor, but not when they meet the result."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1304_7054_amd as kron
+
+pytestmark = pytest.mark.gpu
+
+NP = {"f32": np.float32, "f64": np.float64}
+TOL = {"f32": 1e-5, "f64": 1e-13}
+
+
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _call(mode, d, n, ops, alpha, factors, X, beta, Y, batch):
+    ty = torch.from_numpy(Y.copy()).cuda()
+    getattr(kron, f"kron_nd_batched_{mode}")([n] * d, [n] * d, ops, alpha, [torch.from_numpy(f).cuda() for f in factors],
+                                             torch.from_numpy(X).cuda(), beta, ty, batch)
+    torch.cuda.synchronize()
+    return ty.cpu().numpy()
+
+
+@pytest.mark.parametrize("large", [False, True])
+@pytest.mark.parametrize("d,n", [(2, 4), (2, 16), (3, 10), (3, 16)])
+@pytest.mark.parametrize("mode", list(NP))
+def test_alpha_scales_the_result(mode, d, n, large):
+    """alpha * F_0 overflows (large) or is subnormal; the products and the
+    scaled result are ordinary numbers."""
+    _need_gpu()
+    dt = NP[mode]
+    alpha, f0, x = {("f32", True): (1e25, 1e20, 1e-30), ("f32", False): (1e-25, 1e-18, 1e30),
+                    ("f64", True): (1e200, 1e150, 1e-250), ("f64", False): (1e-200, 1e-120, 1e250)}[mode, large]
+    rng = np.random.default_rng(17)
+    factors = [rng.uniform(-1, 1, n * n).astype(dt) for _ in range(d)]
+    factors[0] = (factors[0] * f0).astype(dt)
+    for batch in (1, 40):
+        X = (rng.standard_normal(batch * n ** d) * x).astype(dt)
+        got = _call(mode, d, n, "NT" if d == 2 else "TNC", alpha, factors, X, 0.0, np.zeros(batch * n ** d, dt), batch)
+        want = oracle.kron_nd([n] * d, [n] * d, "NT" if d == 2 else "TNC", float(dt(alpha)), factors, X, 0.0,
+                              np.zeros(batch * n ** d), batch)
+        scale = np.abs(want).max()
+        assert np.all(np.isfinite(got)), batch
+        err = np.linalg.norm(got / scale - want / scale) / np.linalg.norm(want / scale)
+        assert err <= TOL[mode], (batch, err)
