@@ -837,13 +837,17 @@ bool fuse_plan(int d, int k0, const int* m, const int* n, const int* opc, const 
 // -1 leave exact; any other alpha belongs to the finished result, because
 // alpha * F_0 can overflow or lose bits where the result would not, and takes
 // the fused kernel (256 MiB, FP32: 3-D n = 10 93 us so and 279 there, 2-D
-// n = 16 94 and 149).
+// n = 16 94 and 149).  beta != 0 stays here in FP32 for n = 4, 8 and 16, whose
+// register tiles have no empty slots and rows of 16-byte vectors (256 MiB, 3-D
+// n = 8 171 us, fused 251); the beta kernel of the other sizes and of FP64 moves
+// single elements (2-D n = 12 391 us, fused 176; FP64 462 and 150).
 template <typename T>
 bool nd_plain(int d, const int* m, const int* n, const int* opc, T alpha, const T* const* F, const int* ldf,
               const int64_t* ldfp, const T* X, T beta, T* Y, int64_t batch, void* ws, size_t need, hipStream_t stream) {
   if ((d != 2 && d != 3) || (alpha != T(1) && alpha != T(-1))) return false;
   const int N = n[0];
   if (N > KRON_MAX_N) return false;
+  if (beta != T(0) && (sizeof(T) == 8 || N < 4 || 16 % N != 0)) return false;
   for (int k = 0; k < d; ++k)
     if (m[k] != N || n[k] != N || ldfp[k] != 0) return false;
   if (need < (size_t)d * N * N * sizeof(T)) return false;
@@ -852,12 +856,12 @@ bool nd_plain(int d, const int* m, const int* n, const int* opc, T alpha, const 
   T* P = static_cast<T*>(ws);
   prepare_factors(N, d, F, ldf, tmask, alpha, P, stream);
   const T *A = P, *B = P + N * N, *C = P + 2 * N * N;
-  if (beta != T(0)) {
-    if constexpr (sizeof(T) == 8) d == 2 ? ex2d_f64(N, A, B, X, Y, batch, beta, false, stream) : ex3d_f64(N, A, B, C, X, Y, batch, beta, stream);
-    else d == 2 ? ex2d_f32(N, A, B, X, Y, batch, beta, false, stream) : ex3d_f32(N, A, B, C, X, Y, batch, beta, stream);
+  if constexpr (sizeof(T) == 8) {
+    d == 2 ? fwd2d_f64(N, A, B, X, Y, batch, stream, false) : fwd3d_f64(N, A, B, C, X, Y, batch, stream, false);
+  } else if (beta != T(0)) {
+    d == 2 ? ex2d_f32(N, A, B, X, Y, batch, beta, false, stream) : ex3d_f32(N, A, B, C, X, Y, batch, beta, stream);
   } else {
-    if constexpr (sizeof(T) == 8) d == 2 ? fwd2d_f64(N, A, B, X, Y, batch, stream, false) : fwd3d_f64(N, A, B, C, X, Y, batch, stream, false);
-    else d == 2 ? fwd2d_f32(N, A, B, X, Y, batch, stream, false) : fwd3d_f32(N, A, B, C, X, Y, batch, stream, false);
+    d == 2 ? fwd2d_f32(N, A, B, X, Y, batch, stream, false) : fwd3d_f32(N, A, B, C, X, Y, batch, stream, false);
   }
   return true;
 }

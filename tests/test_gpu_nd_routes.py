@@ -1,6 +1,9 @@
 """The general action on packed real cubes up to n = 16, whose products the
 plain 2-D / 3-D kernels can take, against the oracle: scales that leave the
-type's range when they meet a factor, but not when they meet the result."""
+type's range when they meet a factor, but not when they meet the result; and
+the launches of a call."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -49,3 +52,36 @@ def test_alpha_scales_the_result(mode, d, n, large):
         assert np.all(np.isfinite(got)), batch
         err = np.linalg.norm(got / scale - want / scale) / np.linalg.norm(want / scale)
         assert err <= TOL[mode], (batch, err)
+
+
+def _captured_nodes(fn):
+    """Nodes of the graph that one call records."""
+    fn()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        fn()
+    count = ctypes.c_size_t(0)
+    hip = kron.lib()  # its symbols include the HIP runtime it is linked to
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+    return count.value
+
+
+@pytest.mark.parametrize("mode,d,n", [("f32", 2, 12), ("f32", 3, 7), ("f64", 2, 16), ("f64", 3, 3)])
+def test_beta_in_one_launch(mode, d, n):
+    """beta != 0 at sizes whose beta kernel pads its tiles or moves single
+    elements: one launch of the fused kernel, without prepared factors."""
+    _need_gpu()
+    dt = NP[mode]
+    rng = np.random.default_rng(18)
+    batch, ops = 50, "TN" if d == 2 else "NTC"
+    factors = [rng.standard_normal(n * n).astype(dt) for _ in range(d)]
+    X, Y0 = (rng.standard_normal(batch * n ** d).astype(dt) for _ in range(2))
+    tf, tx, ty = [torch.from_numpy(f).cuda() for f in factors], torch.from_numpy(X).cuda(), torch.from_numpy(Y0).cuda()
+    code = kron.MODE_F32 if mode == "f32" else kron.MODE_F64
+    ws = torch.empty(kron.kron_nd_workspace_size([n] * d, [n] * d, batch, code), dtype=torch.uint8, device="cuda")
+    fn = getattr(kron, f"kron_nd_batched_{mode}")
+    assert _captured_nodes(lambda: fn([n] * d, [n] * d, ops, 1.0, tf, tx, 0.5, ty, batch, ws=ws)) == 1
+    got = _call(mode, d, n, ops, 1.0, factors, X, 0.5, Y0, batch)
+    want = oracle.kron_nd([n] * d, [n] * d, ops, 1.0, factors, X, 0.5, Y0, batch)
+    assert np.linalg.norm(got - want) <= TOL[mode] * np.linalg.norm(want)
