@@ -253,6 +253,8 @@ typedef struct kron_c64 {
    device memory through the caller's workspace `ws` (16-byte aligned, at
    least kron_nd_workspace_size(d, m, n, batch, type) bytes; none for d = 1)
    with type KRON_MODE_F32, KRON_MODE_F64, KRON_TYPE_C32 or KRON_TYPE_C64.
+   With that workspace an operand's result does not depend, to the last bit,
+   on the batch it is in.
    Returns 0, -k (argument k invalid: 1 d, 2 m, 3 n, 4 ops, 6 factors, 7 ldf,
    8 ldfp, 9 X, 11 Y, 12 batch, 13 ws, 14 ws_bytes) or a positive hipError_t;
    asynchronous on `stream`. */

@@ -635,6 +635,25 @@ size_t nd_ws_bytes(int d, const int* m, const int* n, int64_t batch, size_t elem
   return one * (size_t)copies;
 }
 
+// The extent of square real 2-D and 3-D actions that the plain kernels take
+// (nd_plain below), else 0.
+int plain_extent(int d, const int* m, const int* n) {
+  if ((d != 2 && d != 3) || n[0] > KRON_MAX_N) return 0;
+  for (int k = 0; k < d; ++k)
+    if (m[k] != n[0] || n[k] != n[0]) return 0;
+  return n[0];
+}
+
+// What the query returns: the passes' need, and room for the plain kernels'
+// prepared factors, which a batch of one 2-D operand would not have.  With it
+// the route, and so an operand's result, does not depend on the batch; a call
+// with less, down to nd_ws_bytes, runs fused.
+size_t nd_query_bytes(int d, const int* m, const int* n, int64_t batch, size_t elem, bool real) {
+  const size_t need = nd_ws_bytes(d, m, n, batch, elem);
+  const int N = real && batch > 0 ? plain_extent(d, m, n) : 0;
+  return std::max(need, ((size_t)d * N * N * elem + 255) / 256 * 256);
+}
+
 bool sizes_ok(int d, const int* m, const int* n) {
   if (d < 1 || d > kNdMaxDim || !m || !n) return false;
   double ex = 1, ey = 1;
@@ -843,14 +862,14 @@ bool fuse_plan(int d, int k0, const int* m, const int* n, const int* opc, const 
 // single elements (2-D n = 12 391 us, fused 176; FP64 462 and 150).
 template <typename T>
 bool nd_plain(int d, const int* m, const int* n, const int* opc, T alpha, const T* const* F, const int* ldf,
-              const int64_t* ldfp, const T* X, T beta, T* Y, int64_t batch, void* ws, size_t need, hipStream_t stream) {
-  if ((d != 2 && d != 3) || (alpha != T(1) && alpha != T(-1))) return false;
-  const int N = n[0];
-  if (N > KRON_MAX_N) return false;
+              const int64_t* ldfp, const T* X, T beta, T* Y, int64_t batch, void* ws, size_t ws_bytes,
+              hipStream_t stream) {
+  const int N = plain_extent(d, m, n);
+  if (N == 0 || (alpha != T(1) && alpha != T(-1))) return false;
   if (beta != T(0) && (sizeof(T) == 8 || N < 4 || 16 % N != 0)) return false;
   for (int k = 0; k < d; ++k)
-    if (m[k] != N || n[k] != N || ldfp[k] != 0) return false;
-  if (need < (size_t)d * N * N * sizeof(T)) return false;
+    if (ldfp[k] != 0) return false;
+  if (ws_bytes < (size_t)d * N * N * sizeof(T)) return false;
   unsigned tmask = 0;
   for (int k = 0; k < d; ++k) tmask |= opc[k] != 0 ? 1u << k : 0u;
   T* P = static_cast<T*>(ws);
@@ -949,7 +968,7 @@ int nd_run(int d, const int* m, const int* n, const char* ops, T ar, T ai, const
   int which = 0;
   if constexpr (!kC) {
     if (packed(d, n, xs) && packed(d, m, ys) &&
-        nd_plain(d, m, n, opc, ar, F, ldf, ldfp, X, br, Y, batch, ws, need, stream))
+        nd_plain(d, m, n, opc, ar, F, ldf, ldfp, X, br, Y, batch, ws, ws_bytes, stream))
       return 0;
   }
   // The products over the fastest indices, as many as fit, in one kernel; the
@@ -1053,7 +1072,7 @@ size_t kron_nd_workspace_size(int d, const int* m, const int* n, int64_t batch, 
     case KRON_TYPE_C64: elem = 16; break;
     default: return 0;
   }
-  return kron::nd_ws_bytes(d, m, n, batch, elem);
+  return kron::nd_query_bytes(d, m, n, batch, elem, type == KRON_MODE_F32 || type == KRON_MODE_F64);
 }
 
 int kron_nd_batched_f32(int d, const int* m, const int* n, const char* ops, float alpha, const float* const* factors,

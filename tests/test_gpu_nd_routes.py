@@ -85,3 +85,22 @@ def test_beta_in_one_launch(mode, d, n):
     got = _call(mode, d, n, ops, 1.0, factors, X, 0.5, Y0, batch)
     want = oracle.kron_nd([n] * d, [n] * d, ops, 1.0, factors, X, 0.5, Y0, batch)
     assert np.linalg.norm(got - want) <= TOL[mode] * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("n", [1, 4, 6, 11, 16])
+@pytest.mark.parametrize("d", [2, 3])
+@pytest.mark.parametrize("mode", list(NP))
+def test_result_does_not_depend_on_the_batch(mode, d, n):
+    """One operand alone, in the workspace that the query names for it, gives
+    the bits that it has inside a batch."""
+    _need_gpu()
+    dt = NP[mode]
+    rng = np.random.default_rng(19)
+    factors = [rng.standard_normal(n * n).astype(dt) for _ in range(d)]
+    e = n ** d
+    X = rng.standard_normal(5 * e).astype(dt)
+    for ops in ("NNN", "TNT", "CCC"):
+        whole = _call(mode, d, n, ops[:d], 1.0, factors, X, 0.0, np.zeros_like(X), 5)
+        for p in (0, 4):
+            one = _call(mode, d, n, ops[:d], 1.0, factors, X[p * e:(p + 1) * e].copy(), 0.0, np.zeros(e, dt), 1)
+            assert np.array_equal(one, whole[p * e:(p + 1) * e]), (ops, p)
