@@ -85,8 +85,9 @@ inline bool vec_strides(const Strides& s, const void* base) {
 // The strided action on columns in LDS (kron_strided_cols.hip) of prepared
 // factors; false, with nothing launched, where the general kernel is used:
 // operands so far apart that offsets in a tile need more than 32 bits, and
-// n = 16 with rows for 16-byte vectors, whose tiles waste nothing and equal the
-// dense kernels' results to the last bit (3-D FP32 padded by 4, 671 MB of X:
+// n = 16 with rows for 16-byte vectors (but for FP64 3-D without beta), whose
+// tiles waste nothing and contract in the order of the packed call's kernel, so
+// that the results equal it to the last bit (3-D FP32 padded by 4, 671 MB of X:
 // 413 us, columns 449; padded by 1, 128 MiB: 93, columns 56), or FP32
 // beyond 320 MiB (3-D padded by 1, 512 MiB: 337, columns 365; 256: 179, 150).
 bool strided_cols(int dim, int n, const float* A, const float* B, const float* C, const float* X, const Strides& xs,
