@@ -726,12 +726,6 @@ const char* kron_status_string(int status) {
   return hipGetErrorString((hipError_t)status);
 }
 
-namespace {
-// The column kernels have no variant number: callers see a pair that the
-// autotuner never tries.
-kron::LaunchShape reported_shape(kron::LaunchShape s) { return s.blocks_per_cu < 0 ? kron::LaunchShape{64, 8} : s; }
-}  // namespace
-
 const char* kron_version(void) { return "kron 0.1 gfx950"; }
 
 int kron_set_launch(int mode, int dim, int n, int blocks_per_cu, int variant) {
@@ -829,7 +823,7 @@ int kron_autotune(int mode, int dim, int n, const void* A, const void* B, const 
     return rc;
   }
   kron::set_launch_shape(mode, dim, n, bb, bv);
-  const kron::LaunchShape kept = reported_shape(kron::launch_shape(mode, dim, n));
+  const kron::LaunchShape kept = kron::launch_shape(mode, dim, n);
   if (best_blocks) *best_blocks = kept.blocks_per_cu;
   if (best_variant) *best_variant = kept.variant;
   if (best_ms) *best_ms = best;
@@ -842,7 +836,7 @@ int kron_get_launch(int mode, int dim, int n, int* blocks_per_cu, int* variant) 
   if (n < 1 || n > 16) return -3;
   if (!blocks_per_cu) return -4;
   if (!variant) return -5;
-  const kron::LaunchShape sh = reported_shape(kron::launch_shape(mode, dim, n));
+  const kron::LaunchShape sh = kron::launch_shape(mode, dim, n);
   *blocks_per_cu = sh.blocks_per_cu;
   *variant = sh.variant;
   return 0;

@@ -18,11 +18,6 @@ MODES = {"f32": kb.MODE_F32, "f64": kb.MODE_F64, "bf16x3": kb.MODE_BF16X3, "bf16
          "bf16x6": kb.MODE_BF16X6}
 
 
-# how the library reports its column kernels, the built-in default of their
-# sizes, which no launch variant names; such an entry is stored as "builtin"
-COLUMNS = (64, 8)
-
-
 def device_key():
     import torch
     props = torch.cuda.get_device_properties(0)
@@ -45,10 +40,7 @@ def tune_case(mode, dim, n, target_bytes=256 << 20, reps=10):
     Y = torch.empty_like(X)
     mats = [torch.rand(n * n, generator=gen, device="cuda").to(dt) for _ in range(3)]
     b, v, ms = kb.kron_autotune(MODES[mode], dim, n, *mats[:3], X, Y, batch, reps)
-    entry = {"blocks_per_cu": b, "variant": v, "ms": ms, "batch": batch}
-    if (b, v) == COLUMNS:
-        entry["builtin"] = True
-    return entry
+    return {"blocks_per_cu": b, "variant": v, "ms": ms, "batch": batch}
 
 
 def save(table, path):
@@ -67,6 +59,7 @@ def load(path):
         if len(parts) != 5 or "|".join(parts[:2]) != dev:
             continue
         mode, dim, n = parts[2], int(parts[3]), int(parts[4])
+        # "builtin" marks the built-in default in tables that hold another pair for it
         blocks, variant = (-1, 0) if e.get("builtin") else (int(e["blocks_per_cu"]), int(e["variant"]))
         kb.kron_set_launch(MODES[mode], dim, n, blocks, variant)
         applied += 1
