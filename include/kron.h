@@ -487,9 +487,10 @@ int kron3d_backward_f64(int n, const double* A, const double* B, const double* C
    and one sum of the partial gradients.  Groups that ask for dX alone are spread,
    largest first, over eight streams the library owns (per device, created on
    the first such call, default priority, never freed), which wait for the work
-   already on `stream` and which `stream` waits for afterwards (events); one
-   such group, or a device where the streams cannot be created, runs on
-   `stream` itself.  Asynchronous with respect to the host.
+   that was on `stream` before the call, not for the shared launches, and which
+   `stream` waits for afterwards (events); one such group, or a device where the
+   streams cannot be created, runs on `stream` itself.  Asynchronous with respect
+   to the host.
    Returns 0; -1 (groups NULL or an invalid descriptor), -2 (ngroups < 1), -3
    (ws NULL while needed), -4 (ws_bytes too small), or a positive
    hipError_t.  The result of every group is the single-group call's, bit for

@@ -7,6 +7,7 @@
 #include <atomic>
 #include <cstdint>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <vector>
 
@@ -506,46 +507,53 @@ int grad_group_dx(const kron_group_grad_t& d, hipStream_t s) {
   return kron::fwd3d_f64(d.n, (const T*)d.A, (const T*)d.B, (const T*)d.C, (const T*)d.dY, (T*)d.dX, d.count, s, true);
 }
 
-// The dX-only groups.  Fork: the worker streams wait for the work already on
-// `stream`; the groups go to them, largest first, each to the stream with the
-// least work so far (elements read and written, plus a fixed cost for the
-// launch); join: `stream` waits for every worker.  Without worker streams (or
-// with one group) they run on `stream` in descriptor order.
-int grad_groups_dx(std::vector<const kron_group_grad_t*>& groups, hipStream_t stream) {
+// The dX-only groups, beside `other`, which launches the rest of the call on
+// `stream` and returns a status.  Fork: the worker streams wait for the work
+// that was on `stream` before the call, and not for the rest's (5 groups, two of
+// them dX alone, FP64, 300,000 operands: 923 us when they waited, 777 now;
+// 2,000 operands 176 and 78); the groups go to them, largest first, each to the
+// stream with the least work so far (elements read and written, plus a fixed
+// cost for the launch); join: `stream` waits for every worker.  One group runs
+// on `stream` after the rest, because the events cost more than it gains (beside
+// another group, FP32: 2,000 operands 29 us, on a worker 51; 300,000 327 and
+// 331), and so do all without worker streams, in descriptor order.
+int grad_groups_dx(std::vector<const kron_group_grad_t*>& groups, hipStream_t stream,
+                   const std::function<int()>& other) {
   const hipStream_t* workers = groups.size() > 1 ? bwd_streams() : nullptr;
+  const int nw = (int)std::min(groups.size(), (size_t)kBwdStreams);
   hipEvent_t fork = nullptr;
   if (workers) {
     if (hipEventCreateWithFlags(&fork, hipEventDisableTiming) != hipSuccess) {
       workers = nullptr;
     } else {
       hipError_t e = hipEventRecord(fork, stream);
-      for (int w = 0; w < kBwdStreams && e == hipSuccess; ++w) e = hipStreamWaitEvent(workers[w], fork, 0);
+      for (int w = 0; w < nw && e == hipSuccess; ++w) e = hipStreamWaitEvent(workers[w], fork, 0);
       if (e != hipSuccess) {
         (void)hipEventDestroy(fork);
         return (int)e;
       }
     }
   }
+  int rc = other();
   auto cost = [](const kron_group_grad_t* d) {
     return 3.0 * (double)d->count * (d->dim == 3 ? (double)d->n * d->n * d->n : (double)d->n * d->n) + 2.0e5;
   };
   if (workers)
     std::stable_sort(groups.begin(), groups.end(), [&](auto* a, auto* b) { return cost(a) > cost(b); });
   double load[kBwdStreams] = {};
-  int rc = 0;
   for (const kron_group_grad_t* d : groups) {
+    if (rc != 0) break;
     hipStream_t s = stream;
     if (workers) {
-      const int w = (int)(std::min_element(load, load + kBwdStreams) - load);
+      const int w = (int)(std::min_element(load, load + nw) - load);
       load[w] += cost(d);
       s = workers[w];
     }
     // descriptors were checked, so only a launch failure can end the loop
     rc = finish_launch(grad_group_dx(*d, s));
-    if (rc != 0) break;
   }
   if (workers) {
-    for (int w = 0; w < kBwdStreams; ++w) {
+    for (int w = 0; w < nw; ++w) {
       hipEvent_t done = nullptr;
       hipError_t e = hipEventCreateWithFlags(&done, hipEventDisableTiming);
       if (e == hipSuccess) e = hipEventRecord(done, workers[w]);
@@ -583,11 +591,12 @@ int kron_grouped_backward(const kron_group_grad_t* groups, int ngroups, void* ws
     else if (d.dX && d.count > 0) dx.push_back(&d);
     slice += b;
   }
-  if (!full.empty()) {
+  auto shared = [&] {
+    if (full.empty()) return 0;
     kron::backward_grouped(full, stream);
-    if (int rc = finish_launch(0)) return rc > 0 ? rc : -1;
-  }
-  const int rc = dx.empty() ? 0 : grad_groups_dx(dx, stream);
+    return finish_launch(0);
+  };
+  const int rc = dx.empty() ? shared() : grad_groups_dx(dx, stream, shared);
   return rc < 0 ? -1 : rc;
 }
 
