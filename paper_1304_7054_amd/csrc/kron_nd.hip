@@ -774,36 +774,47 @@ bool fuse_plan(int d, int k0, const int* m, const int* n, const int* opc, const 
     for (int j = k0; j < d; ++j) c *= j < k ? n[j] : j > k ? m[j] : 1;
     cols += c;
   }
+  // bytes of the factors that a tile shares, and of an operand's own
+  const bool per_op = P.per_operand && P.per == 1;
   const double images = (size[0] + size[1]) * (double)elem;
-  const bool table = fac * (double)elem + images + 4 * cols <= (double)kFuseLds;
-  const double one = images + (table ? 4 * cols : 0);
-  if (fac * (double)elem + one > (double)kFuseLds) return false;
+  const double shared = per_op ? 0 : fac * (double)elem, own = per_op ? fac * (double)elem : 0;
+  const bool table = shared + own + images + 4 * cols <= (double)kFuseLds;
+  const double one = own + images + (table ? 4 * cols : 0);
+  if (shared + one > (double)kFuseLds) return false;
+  // tiles for every CU first; of those, the count whose column blocks fill the
+  // four wavefronts' rounds best.  Factors of their own take most of an operand's
+  // LDS and leave a small operand's wavefronts idle, so they may take more of it
+  // where the rounds saved outweigh the workgroups that a CU then holds (256 MiB,
+  // complex 16 x 16 to 17 x 17: 375 us within kFuseTile, 320 beyond; without the
+  // condition FP32 2 x 2 3,160 and 3,820, 64 x 4 236 and 274).
+  const int64_t room = slices / (2 * device_cus());
+  const int64_t fill = std::max<int64_t>(1, std::min((int64_t)((double)kFuseTile / one), room));
+  const int64_t most = std::max(fill, std::min((int64_t)((double)(per_op ? 2 * kFuseTile : kFuseTile) / one), room));
+  auto per_cu = [&](int64_t o) { return std::floor(std::min(8.0, 160.0 * 1024 / (shared + (double)o * one))); };
   int64_t ops = 1;
-  if (!P.per_operand) {
-    ops = std::min<int64_t>((int64_t)((double)kFuseTile / one), (int64_t)(((double)kFuseLds - fac * (double)elem) / one));
-    ops = std::min(ops, slices / (2 * device_cus()));  // tiles for every CU first
-    // of those, the count whose column blocks fill the four wavefronts' rounds best
-    const int64_t most = std::max<int64_t>(ops, 1);
-    double best = 1e300;
-    for (int64_t o = 1; o <= most; ++o) {
-      double cost = 0;
-      for (int k = k0; k < d; ++k) {
-        int64_t cols = o;
-        for (int j = k0; j < d; ++j) cols *= j < k ? n[j] : j > k ? m[j] : 1;
-        const int64_t rounds = ((cols + 15) / 16 + 4 * blocks - 1) / (4 * blocks);
-        cost += (double)rounds * ((m[k] + 15) / 16) * ((n[k] + 3) / 4);
-      }
-      if (cost / (double)o <= best) {
-        best = cost / (double)o;
-        ops = o;
-      }
+  double best = 1e300;
+  for (int64_t o = 1; o <= most; ++o) {
+    if (P.per_operand && !per_op && P.per % o != 0) continue;  // slices of one operand
+    double cost = 0;
+    for (int k = k0; k < d; ++k) {
+      int64_t cols = per_op ? 1 : o;
+      for (int j = k0; j < d; ++j) cols *= j < k ? n[j] : j > k ? m[j] : 1;
+      const int64_t takes = ((cols + 15) / 16 + blocks - 1) / blocks * (per_op ? o : 1);
+      cost += (double)((takes + 3) / 4) * ((m[k] + 15) / 16) * ((n[k] + 3) / 4);
+    }
+    cost /= (double)o;
+    if (o <= fill ? cost <= best : cost / per_cu(o) < best / per_cu(ops)) {
+      best = cost;
+      ops = o;
     }
   }
   P.ops = (int)ops;
   P.batch = slices;
   P.ntiles = (slices + ops - 1) / ops;
   int at = 0, tab = 0;
-  const int base[2] = {(int)fac, (int)fac + (int)(ops * size[0])};
+  P.facs = (int)fac;
+  const int first = (int)fac * (per_op ? (int)ops : 1);
+  const int base[2] = {first, first + (int)(ops * size[0])};
   P.img_x = base[0];
   P.img_y = base[image[ns]];
   for (int q = 0; q < ns; ++q) {
@@ -813,6 +824,8 @@ bool fuse_plan(int d, int k0, const int* m, const int* n, const int* opc, const 
     st.m = m[k];
     st.ks = (n[k] + 3) / 4;
     st.rb = (m[k] + 15) / 16;
+    st.frags = fast_div((uint32_t)(st.rb * st.ks));
+    st.steps = fast_div((uint32_t)st.ks);
     int pre = 1, post = 1;
     for (int j = k0; j < k; ++j) pre *= n[j];
     for (int j = k + 1; j < d; ++j) post *= m[j];
@@ -889,7 +902,9 @@ bool packed(int d, const int* ext, const NdStrides* st);
 
 template <typename T, bool kC, int kKS, int kCB>
 void fuse_launch(const FusedArgs& P, size_t lds, bool beta, T ar, T ai, T br, T bi, hipStream_t stream) {
-  auto k = beta ? kron_nd_fused_kernel<T, kC, kKS, kCB, true> : kron_nd_fused_kernel<T, kC, kKS, kCB, false>;
+  auto k = P.per_operand ? beta ? kron_nd_fused_kernel<T, kC, kKS, kCB, true, true> : kron_nd_fused_kernel<T, kC, kKS, kCB, false, true>
+           : beta        ? kron_nd_fused_kernel<T, kC, kKS, kCB, true, false>
+                         : kron_nd_fused_kernel<T, kC, kKS, kCB, false, false>;
   const int64_t per_cu = std::min<int64_t>(8, 160 * 1024 / (int64_t)lds);
   const int64_t cap = (int64_t)device_cus() * per_cu;
   hipLaunchKernelGGL(k, dim3((unsigned)std::min(P.ntiles, cap)), dim3(256), lds, stream, P,

@@ -12,8 +12,9 @@
 // all other indices of all P operands flattened, so columns are never padded;
 // lane (L, g) reads elements 4s + g of column L.  Rows of the fastest index
 // sit at a pitch that lets 16 columns be read side by side without meeting an
-// LDS bank twice.  The factors are laid out in LDS once, as the fragments that
-// the instruction takes (with factors per operand, once per operand).
+// LDS bank twice.  The factors are laid out in LDS as the fragments that the
+// instruction takes: once, or, with factors per operand, those of every operand
+// of the tile, whose blocks of columns then hold one operand's only.
 #pragma once
 
 #include "kron_cols.hpp"
@@ -42,6 +43,7 @@ struct FusedStage {
   int in_u, in_s, out_u, out_s, pitch;
   int in, out;            // LDS offsets of the images (the same one when m == n)
   FastDiv post, fast;
+  FastDiv frags, steps;   // fragments of the factor: rb * ks, and ks
   int fac;                // LDS offset of the factor's fragments
   int tab;                // first entry of the tile's columns in the offset table
   const void* F;
@@ -65,7 +67,8 @@ struct FusedArgs {
   int64_t per;            // slices per operand (the operand of slice i is i / per)
   int img_x, img_y;       // LDS offsets of the first and the last image
   int table;              // bytes before the offset table (-1: no room for one)
-  int per_operand;        // factors change with the operand (then ops == 1)
+  int per_operand;        // factors change with the operand: a tile's slices are of one, or its operands whole
+  int facs;               // LDS elements of one operand's fragments
   int conjx;
   FusedArray x, y;
   FusedStage st[kFuseMax];
@@ -103,10 +106,12 @@ __device__ __forceinline__ uint32_t fused_column(const FusedStage& st, uint32_t 
 }
 
 // One product of a tile by one wavefront of four: kCB blocks of 16 columns at a
-// time, their kKS steps of four elements in registers (st.ks == kKS).
-template <typename T, bool kC, int kKS, int kCB>
+// time, their kKS steps of four elements in registers (st.ks == kKS).  kVar:
+// `sets` operands have factors of their own, facs elements apart, and ncols
+// columns each; else all ncols columns of the tile share one.
+template <typename T, bool kC, int kKS, int kCB, bool kVar>
 __device__ __forceinline__ void fused_stage(const FusedStage& st, typename FusedElem<T, kC>::type* base,
-                                            const uint32_t* tab, int nops, int wave, int lane) {
+                                            const uint32_t* tab, int sets, int ncols, int facs, int wave, int lane) {
   using elem_t = typename FusedElem<T, kC>::type;
   using acc_t = std::conditional_t<sizeof(T) == 8, f64x4, f32x4>;
   auto mma = [](T a, T b, acc_t c) {
@@ -116,10 +121,22 @@ __device__ __forceinline__ void fused_stage(const FusedStage& st, typename Fused
   const int L = lane & 15, g = lane >> 4;
   const elem_t* in = base + st.in;
   elem_t* out = base + st.out;
-  const elem_t* fac = base + st.fac + lane;
-  const int ncols = nops * st.cols, in_s = st.in_s, out_s = st.out_s;
+  const int in_s = st.in_s, out_s = st.out_s;
   const bool last_in = 4 * (kKS - 1) + g < st.n;  // whether the last step's element exists
-  for (int c0 = 16 * kCB * wave; c0 < ncols; c0 += 16 * kCB * 4) {
+  const elem_t* fac = base + st.fac + lane;
+  int first = 0;  // the set's first column
+  for (int c0 = 16 * kCB * wave;; c0 += 16 * kCB * 4) {
+    if constexpr (kVar) {
+      while (c0 >= ncols && sets > 0) {
+        c0 -= (ncols + 16 * kCB - 1) / (16 * kCB) * (16 * kCB);
+        first += ncols;
+        fac += facs;
+        --sets;
+      }
+      if (sets == 0) break;
+    } else {
+      if (c0 >= ncols) break;
+    }
     T x[kCB][kKS], xi[kC ? kCB : 1][kC ? kKS : 1];
     elem_t* dst[kCB];
     bool ok[kCB];
@@ -128,7 +145,7 @@ __device__ __forceinline__ void fused_stage(const FusedStage& st, typename Fused
       // lanes past the last column read it again and write nothing
       const int cw = c0 + 16 * b + L;
       ok[b] = cw < ncols;
-      const uint32_t c = ok[b] ? cw : ncols - 1;
+      const uint32_t c = (ok[b] ? cw : ncols - 1) + first;
       const uint32_t at = tab ? in_lds(tab)[st.tab + c] : fused_column(st, c);
       const elem_t* col = in + (at & 0xffff) + g * in_s;
       dst[b] = out + (at >> 16) + (sizeof(T) == 8 ? g : 4 * g) * out_s;
@@ -195,7 +212,7 @@ constexpr int fused_waves() {
   return sizeof(T) == 4 ? 5 : kKS <= 4 ? 4 : 3;
 }
 
-template <typename T, bool kC, int kKS, int kCB, bool kBeta>
+template <typename T, bool kC, int kKS, int kCB, bool kBeta, bool kVar>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fused_waves<T, kC, kKS>()))) void kron_nd_fused_kernel(
     FusedArgs P, FastDiv xe, FastDiv ye, T ar, T ai, T br, T bi) {
   using elem_t = typename FusedElem<T, kC>::type;
@@ -206,25 +223,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fused_waves
   elem_t* const base = reinterpret_cast<elem_t*>(fused_lds);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // the fragments of every factor: (row block, step) by lane
-  auto load_factors = [&](int64_t operand) {
+  // the fragments of every factor of `count` operands: (row block, step) by lane
+  auto load_factors = [&](int64_t operand, int count) {
     for (int q = 0; q < P.nstage; ++q) {
       const FusedStage st = P.st[q];
       const T* F = static_cast<const T*>(st.F) + operand * st.ldfp * kS;
-      for (int e = tid; e < st.rb * st.ks * 64; e += 256) {
-        const int f = e >> 6, i = 16 * (f / st.ks) + (e & 15), k = 4 * (f % st.ks) + ((e >> 4) & 3);
+      for (int e = tid; e < count * (int)st.frags.d * 64; e += 256) {
+        const uint32_t f = e >> 6, op = kVar ? st.frags.div(f) : 0, h = f - op * st.frags.d, rb = st.steps.div(h);
+        const int i = 16 * rb + (e & 15), k = 4 * (h - rb * st.steps.d) + ((e >> 4) & 3);
         T re = 0, im = 0;
         if (i < st.m && k < st.n) {
-          const int64_t o = st.op == 0 ? i + (int64_t)st.ld * k : k + (int64_t)st.ld * i;
+          const int64_t o = (st.op == 0 ? i + (int64_t)st.ld * k : k + (int64_t)st.ld * i) + op * st.ldfp;
           re = in_global(F)[kS * o];
           if constexpr (kC) im = st.op == 2 ? -in_global(F)[kS * o + 1] : in_global(F)[kS * o + 1];
         }
-        if constexpr (kC) in_lds(base)[st.fac + e] = elem_t{re, im};
-        else in_lds(base)[st.fac + e] = re;
+        const int to = st.fac + (int)(op * P.facs + h * 64) + lane;
+        if constexpr (kC) in_lds(base)[to] = elem_t{re, im};
+        else in_lds(base)[to] = re;
       }
     }
   };
-  if (!P.per_operand) load_factors(0);
+  if constexpr (!kVar) load_factors(0, 1);
   // where each column of a full tile starts in the images, for every product
   uint32_t* const tab = P.table < 0 ? nullptr : reinterpret_cast<uint32_t*>(fused_lds + P.table);
   if (tab) {
@@ -246,14 +265,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fused_waves
     const uint32_t row = P.x.ext[0].div(e);
     *in_lds(reinterpret_cast<vec_t*>(img + row * P.x.pitch + (e - row * P.x.ext[0].d))) = v;
   };
-  for (int64_t t = blockIdx.x; t < P.ntiles; t += gridDim.x) {
+  // a workgroup's tiles; slices of operands with factors of their own one after
+  // the other, so that the factors are read once per operand
+  const bool own = kVar && P.per == 1;
+  int64_t t = blockIdx.x, end = P.ntiles, step = gridDim.x, loaded = -1;
+  if (kVar && !own) {
+    const int64_t share = (P.ntiles + gridDim.x - 1) / gridDim.x;
+    t = blockIdx.x * share;
+    end = t + share < P.ntiles ? t + share : P.ntiles;
+    step = 1;
+  }
+  for (; t < end; t += step) {
     const int64_t rem = P.batch - t * P.ops;
     const int nops = (int)(rem < P.ops ? rem : P.ops);
     const elem_t* X = static_cast<const elem_t*>(P.X) + t * P.ops * (P.x.stride[0] < 0 ? P.x.elems : P.x.sp);
     elem_t* Y = static_cast<elem_t*>(P.Y) + t * P.ops * (P.y.stride[0] < 0 ? P.y.elems : P.y.sp);
-    if (P.per_operand) {
-      lds_barrier();  // the previous operand's products are done
-      load_factors(t / P.per);
+    if constexpr (kVar) {
+      const int64_t operand = own ? t * P.ops : t * P.ops / P.per;
+      if (operand != loaded) load_factors(operand, own ? nops : 1);
+      loaded = operand;
     }
     {
       elem_t* img = base + P.img_x;
@@ -291,7 +321,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fused_waves
       const FusedStage st = P.st[q];
       static_for<kKS>([&](auto i) {
         constexpr int kSteps = decltype(i)::value + 1;
-        if (st.ks == kSteps) fused_stage<T, kC, kSteps, kSteps <= 8 ? kCB : 1>(st, base, tab, nops, wave, lane);
+        if (st.ks == kSteps) fused_stage<T, kC, kSteps, kSteps <= 8 ? kCB : 1, kVar>(
+              st, base, tab, own ? nops : 1, own ? st.cols : nops * st.cols, P.facs, wave, lane);
       });
       lds_barrier();
     }
