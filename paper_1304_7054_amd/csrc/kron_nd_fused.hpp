@@ -147,11 +147,15 @@ __device__ __forceinline__ void fused_stage(const FusedStage& st, typename Fused
       ok[b] = cw < ncols;
       const uint32_t c = (ok[b] ? cw : ncols - 1) + first;
       const uint32_t at = tab ? in_lds(tab)[st.tab + c] : fused_column(st, c);
-      const elem_t* col = in + (at & 0xffff) + g * in_s;
+      const elem_t* top = in + (at & 0xffff);
+      const elem_t* col = top + g * in_s;
+      // where the last step's element does not exist, the column's first one in
+      // its place: beyond the last column the image ends
+      const elem_t* tail = last_in ? col + 4 * (kKS - 1) * in_s : top;
       dst[b] = out + (at >> 16) + (sizeof(T) == 8 ? g : 4 * g) * out_s;
 #pragma unroll
       for (int s = 0; s < kKS; ++s) {
-        const elem_t v = in_lds(col)[4 * s * in_s];
+        const elem_t v = s + 1 < kKS ? in_lds(col)[4 * s * in_s] : *in_lds(tail);
         if constexpr (kC) {
           x[b][s] = v[0];
           xi[b][s] = v[1];
