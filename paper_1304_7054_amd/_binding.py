@@ -360,6 +360,8 @@ def forward_rows(dim, n, mats, X, Y, batch):
     transposed view is contiguous) on FP32 / FP64 operands, on the current
     stream.  Returns the column-major factors, one after the other, which the
     call prepares on the device (unset for an empty batch)."""
+    if not 1 <= n <= 16:
+        raise ValueError(f"n must be in 1..16, got {n}")
     dtype = X.dtype
     ops, rows = [], []
     for M in mats:
@@ -373,7 +375,7 @@ def forward_rows(dim, n, mats, X, Y, batch):
         rows.append(M)
     cols = torch.empty(dim * n * n, dtype=dtype, device=X.device)
     size = batch * n ** dim
-    ptrs = [_arr(M, dtype, n * n, "factor") for M in rows]
+    ptrs = [_arr(M, dtype, n * n, f"factor {i}") for i, M in enumerate(rows)]
     if dim == 2:
         ops.append(b"N")  # op on the operands
     tag = "f32" if dtype == torch.float32 else "f64"
