@@ -438,7 +438,9 @@ struct ColTiles {
 
 // At least two wavefronts per SIMD (at most 256 registers): the compiler then
 // keeps the matrix results in vector registers.  With accumulation registers
-// it merged two LDS stores of n = 8 with the offset of another one.
+// it pairs LDS stores wrongly: FP32 n = 8 stores rows 4 and 5 of a plane as
+// ds_write2_b32 at elements 8 and 40, not 32 and 40, the byte offset 128 divided
+// by 4 twice.  A host test holds every kernel that writes columns to none.
 template <class S>
 __global__ __launch_bounds__(S::kThreads) __attribute__((amdgpu_waves_per_eu(2))) void kron3d_cols_kernel(
     const typename S::io_t* __restrict__ A, const typename S::io_t* __restrict__ B,
