@@ -333,8 +333,13 @@ constexpr int backward_lds() {
 }
 
 // Workgroup `block` of `nblocks`: its tiles and its partial sums.  `which` bit
-// f asks for factor f's gradient; dX may be null (then some gradient is
-// wanted).  Partials: ws[(block * 3 + f) * 256 + row * 16 + col].
+// f asks for factor f's gradient, of at least one; dX may be null.  Partials:
+// ws[(block * 3 + f) * 256 + row * 16 + col].
+//
+// The tests of `which` always hold.  They part loads, LDS writes and products
+// into blocks that the compiler schedules by themselves; without them FP64 3-D
+// n = 8 takes 84 us for dA alone, 63 with (128 MiB of X), n = 10 220 and 209
+// for everything.
 template <class S>
 __device__ __forceinline__ void backward_block(
     typename S::io_t* const lds, const typename S::io_t* __restrict__ A, const typename S::io_t* __restrict__ B,
@@ -382,10 +387,15 @@ __device__ __forceinline__ void backward_block(
         if (which) tl.load_cols(X, t + nblocks, batch, x);
         tl.load_cols(dY, t + nblocks, batch, d);
       }
-      tl.template get<0>(id, d1);
-      tC.template apply<NC>(d1);
-      tl.template put<0>(iw, d1);
-      lds_barrier();
+      // dC alone takes D as it is (FP64, 128 MiB of X: n = 13 140 us with D1, 117
+      // without).  Up to n = 8 and in FP32 it is not bound by the products, and
+      // the test costs the other gradients up to 5 % (FP32 n = 2).
+      if (sizeof(T) == 4 || N <= 8 || wa || wb || dX) {
+        tl.template get<0>(id, d1);
+        tC.template apply<NC>(d1);
+        tl.template put<0>(iw, d1);
+        lds_barrier();
+      }
       if (wa || dX) {
         tl.template get<1>(iw, z);
         tB.template apply<NC>(z);
@@ -467,7 +477,6 @@ __device__ __forceinline__ void backward_block(
       }
     }
   }
-  if (which == 0) return;
   if constexpr (Tiles::kOwn) {
     // 16 lanes an entry: each sums every sixteenth of the lanes' sums
     static_assert(S::kThreads >= 16 * N * N, "16 lanes an entry");
