@@ -547,8 +547,9 @@ int kron_copy_bytes(const void* src, void* dst, size_t bytes, hipStream_t stream
    blocks_per_cu -1 restores the built-in default.  For 3-D FP32 (n < 16),
    FP64 and some bf16 sizes that is none of the variants but the column
    kernels (whole operands in a workgroup's LDS, one column per lane), which
-   kron_get_launch and kron_autotune report as (-1, 0): what they report,
-   kron_set_launch takes back.  The paper
+   kron_get_launch and kron_autotune report as (64, 8); kron_set_launch takes
+   that pair for them at these sizes, so that a reported entry can be set again.
+   The paper
    picks its kernel method by matrix size and fixes the number of thread
    blocks (Sections 4 and 5); here the choice is a per-(mode, dim, n) table
    that an autotuner can fill.  Process-wide, not thread-safe against

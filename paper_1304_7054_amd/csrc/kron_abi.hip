@@ -68,6 +68,16 @@ LaunchShape default_shape(int mode, int dim, int n) {
     default: return LaunchShape{0, 0};
   }
 }
+
+// The column kernels have no variant number.  Where they exist, kron_get_launch
+// and kron_autotune report them as this pair, and kron_set_launch takes it for
+// them: as many workgroups of variant 8 are never the better choice, and the
+// autotuner does not try them.
+constexpr LaunchShape kColumns{64, 8};
+bool is_columns(int mode, int dim, int n, int blocks_per_cu, int variant) {
+  return dim == 3 && has_cols3d(mode, n) && blocks_per_cu == kColumns.blocks_per_cu && variant == kColumns.variant;
+}
+LaunchShape reported_shape(LaunchShape s) { return s.blocks_per_cu < 0 ? kColumns : s; }
 }  // namespace
 
 LaunchShape launch_shape(int mode, int dim, int n) {
@@ -85,6 +95,7 @@ int set_launch_shape(int mode, int dim, int n, int blocks_per_cu, int variant) {
   if (n < 1 || n > 16) return -3;
   if (blocks_per_cu < -1 || blocks_per_cu > 64) return -4;
   if (variant < 0 || variant > (dim == 3 ? 11 : 4)) return -5;
+  if (is_columns(mode, dim, n, blocks_per_cu, variant)) blocks_per_cu = -1;  // they are the default
   g_shape[mode][dim - 2][n].store(blocks_per_cu < 0 ? -1 : blocks_per_cu * 16 + variant, std::memory_order_relaxed);
   return 0;
 }
@@ -832,7 +843,7 @@ int kron_autotune(int mode, int dim, int n, const void* A, const void* B, const 
     return rc;
   }
   kron::set_launch_shape(mode, dim, n, bb, bv);
-  const kron::LaunchShape kept = kron::launch_shape(mode, dim, n);
+  const kron::LaunchShape kept = kron::reported_shape(kron::launch_shape(mode, dim, n));
   if (best_blocks) *best_blocks = kept.blocks_per_cu;
   if (best_variant) *best_variant = kept.variant;
   if (best_ms) *best_ms = best;
@@ -845,7 +856,7 @@ int kron_get_launch(int mode, int dim, int n, int* blocks_per_cu, int* variant) 
   if (n < 1 || n > 16) return -3;
   if (!blocks_per_cu) return -4;
   if (!variant) return -5;
-  const kron::LaunchShape sh = kron::launch_shape(mode, dim, n);
+  const kron::LaunchShape sh = kron::reported_shape(kron::launch_shape(mode, dim, n));
   *blocks_per_cu = sh.blocks_per_cu;
   *variant = sh.variant;
   return 0;

@@ -59,9 +59,7 @@ def load(path):
         if len(parts) != 5 or "|".join(parts[:2]) != dev:
             continue
         mode, dim, n = parts[2], int(parts[3]), int(parts[4])
-        # "builtin" marks the built-in default in tables that hold another pair for it
-        blocks, variant = (-1, 0) if e.get("builtin") else (int(e["blocks_per_cu"]), int(e["variant"]))
-        kb.kron_set_launch(MODES[mode], dim, n, blocks, variant)
+        kb.kron_set_launch(MODES[mode], dim, n, int(e["blocks_per_cu"]), int(e["variant"]))
         applied += 1
     return applied
 
