@@ -155,21 +155,6 @@ int check3d(int n, const void* A, const void* B, const void* C, const void* X, c
   return 0;
 }
 
-// op(M) per factor and alpha on the first factor, written once to `out`
-// (factor f at out + f * n^2, column-major).
-template <typename T>
-__global__ __launch_bounds__(256) void kron_prepare_factors_kernel(int n, int nf, const T* __restrict__ A,
-                                                                   const T* __restrict__ B, const T* __restrict__ C,
-                                                                   unsigned tmask, T alpha, T* __restrict__ out) {
-  const int nn = n * n;
-  for (int e = threadIdx.x; e < nf * nn; e += blockDim.x) {
-    const int f = e / nn, idx = e % nn, i = idx % n, j = idx / n;
-    const T* M = f == 0 ? A : f == 1 ? B : C;
-    const T v = ((tmask >> f) & 1u) ? M[j + n * i] : M[i + n * j];
-    out[e] = f == 0 ? alpha * v : v;
-  }
-}
-
 // 0 for 'N'/'n', 1 for 'T'/'t', -1 otherwise
 int op_bit(char op) { return (op == 'N' || op == 'n') ? 0 : (op == 'T' || op == 't') ? 1 : -1; }
 
@@ -205,8 +190,8 @@ int prepare_ex(int dim, int n, const char* ops, T alpha, const T* const* mats, c
   }
   if (!ws || reinterpret_cast<uintptr_t>(ws) % sizeof(T) != 0) return -(kX + 4);
   if (ws_bytes < (size_t)dim * n * n * sizeof(T)) return -(kX + 5);
-  hipLaunchKernelGGL(kron_prepare_factors_kernel<T>, dim3(1), dim3(256), 0, stream, n, dim, mats[0], mats[1],
-                     dim == 3 ? mats[2] : mats[1], tmask, alpha, static_cast<T*>(ws));
+  const int ld[3] = {n, n, n};
+  kron::prepare_factors(n, dim, mats, ld, tmask, alpha, static_cast<T*>(ws), stream);
   return 0;
 }
 

@@ -1,4 +1,5 @@
-// Column kernels: 3-D operands of n < 16 through workgroup tiles in LDS.
+// Column kernels: 3-D operands through workgroup tiles in LDS (FP32 n < 16, FP64
+// every n, bf16 storage the sizes whose register tiles waste most).
 //
 // A mode product is a small matrix applied to every column (fibre) of the
 // operand along one axis.  A workgroup holds P whole operands, packed back to
@@ -215,7 +216,7 @@ template <int N, typename io_t>
 constexpr ColShape col3d_shape() {
   constexpr ColShape s4[17] = {{0, 0, 0},  {512, 4, 0}, {128, 4, 4}, {56, 4, 4}, {16, 4, 4}, {10, 4, 4},
                                {14, 4, 2}, {15, 6, 1},  {8, 4, 2},   {6, 4, 3},  {4, 7, 3},  {4, 8, 1},
-                               {2, 5, 2},  {1, 3, 4},   {1, 4, 4},   {1, 4, 4},  {1, 4, 4}};
+                               {2, 5, 2},  {1, 3, 4},   {1, 4, 4},   {1, 4, 4},  {0, 0, 0}};
   constexpr ColShape s8[17] = {{0, 0, 0}, {512, 4, 4}, {64, 4, 4}, {28, 4, 3}, {16, 4, 2}, {10, 4, 2},
                                {7, 4, 2}, {10, 8, 1},  {4, 4, 0},  {3, 4, 3},  {1, 2, 0},  {1, 2, 4},
                                {1, 3, 4}, {1, 4, 4},   {1, 7, 2},  {1, 8, 4},  {1, 8, 4}};

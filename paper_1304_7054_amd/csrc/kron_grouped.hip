@@ -15,8 +15,9 @@
 // workgroup loads one group's factors once, and neighbouring tiles run at the
 // same time, as in the single-group kernels.  Persistent wavefronts that claim
 // chunks (as below) swept a thousand separate streams and waited for counters,
-// group changes and chunks that are large for a small batch: 440
-// against 353 us for 500,000 mixed operands, 88 against 13 us for 5,000.
+// group changes and chunks that are large for a small batch; that launch, on
+// padded register tiles, took 413 us for 500,000 mixed operands and 88 for
+// 5,000, this one on column tiles takes 293 and 13.
 //
 // bf16x3 part: a header and, for each of two phases (2-D groups, 3-D groups),
 // the list of its groups with the number of work units before each.  With
@@ -148,10 +149,11 @@ struct Claim {
 // chunk c.  The group's units are u0 .. u1 - 1 of the phase sequence; chunk
 // c holds units cstart[c] .. cstart[c + 1] - 1.  Returns the first claimed
 // chunk that is not this group's (or one past the last chunk).
-template <class M, int N, bool kVec>
+template <int N, bool kVec>
 __device__ __attribute__((noinline)) int64_t run_group_2d(const GroupDesc& gd, int64_t c, const ChunkTable& ct,
                                                           int64_t u0, int64_t u1, Claim cl, int L, int g,
                                                           float* slice) {
+  using M = ModeBF16x3;
   using io_t = typename M::io_t;
   using acc_t = typename M::acc_t;
   const io_t* X = static_cast<const io_t*>(gd.X);
@@ -292,11 +294,12 @@ __device__ __attribute__((noinline)) void sweep_group_2d(const GroupDesc& gd, in
   }
 }
 
-// As run_group_2d for a bf16x3 3-D group (a unit is one tile).
-template <class M, int N, bool kVec>
+// As run_group_2d for a 3-D group (a unit is one tile).
+template <int N, bool kVec>
 __device__ __attribute__((noinline)) int64_t run_group_3d(const GroupDesc& gd, int64_t c, const ChunkTable& ct,
                                                           int64_t u0, int64_t u1, Claim cl, int L, int g,
                                                           float* slice) {
+  using M = ModeBF16x3;
   using io_t = typename M::io_t;
   using acc_t = typename M::acc_t;
   const io_t* X = static_cast<const io_t*>(gd.X);
@@ -356,17 +359,17 @@ __device__ __attribute__((noinline)) int64_t run_group_3d(const GroupDesc& gd, i
   return c;
 }
 
-template <class M, int Dim>
+template <int Dim>
 __device__ __forceinline__ int64_t run_group(const GroupDesc& gd, int64_t c, const ChunkTable& ct, int64_t u0,
                                              int64_t u1, Claim cl, int L, int g, float* slice) {
 #define KRON_G_CASE(NN)                                                                                 \
   case NN:                                                                                              \
     if constexpr (Dim == 2) {                                                                           \
-      if (NN == 16 && gd.vec) return run_group_2d<M, NN, NN == 16>(gd, c, ct, u0, u1, cl, L, g, slice); \
-      return run_group_2d<M, NN, false>(gd, c, ct, u0, u1, cl, L, g, slice);                           \
+      if (NN == 16 && gd.vec) return run_group_2d<NN, NN == 16>(gd, c, ct, u0, u1, cl, L, g, slice);    \
+      return run_group_2d<NN, false>(gd, c, ct, u0, u1, cl, L, g, slice);                              \
     } else {                                                                                            \
-      if (NN == 16 && gd.vec) return run_group_3d<M, NN, NN == 16>(gd, c, ct, u0, u1, cl, L, g, slice); \
-      return run_group_3d<M, NN, false>(gd, c, ct, u0, u1, cl, L, g, slice);                           \
+      if (NN == 16 && gd.vec) return run_group_3d<NN, NN == 16>(gd, c, ct, u0, u1, cl, L, g, slice);    \
+      return run_group_3d<NN, false>(gd, c, ct, u0, u1, cl, L, g, slice);                              \
     }
   switch (gd.n) { KRON_N_CASES(KRON_G_CASE) }
 #undef KRON_G_CASE
@@ -375,7 +378,7 @@ __device__ __forceinline__ int64_t run_group(const GroupDesc& gd, int64_t c, con
 
 // One phase's chunks, claimed until none are left; then the wavefront
 // counts itself out of the phase (the last one resets the phase's counters).
-template <class M, int Dim>
+template <int Dim>
 __device__ __forceinline__ void grouped_phase(const uint8_t* __restrict__ ws, const Header* __restrict__ h,
                                               float* slice) {
   const PhaseDesc& ph = h->phase[Dim - 2];
@@ -394,7 +397,7 @@ __device__ __forceinline__ void grouped_phase(const uint8_t* __restrict__ ws, co
     const int64_t u = ct.first(c);
     while (ubefore[k + 1] <= u) ++k;  // a wavefront's claims only grow
     const GroupDesc gd = groups[list[k]];
-    c = run_group<M, Dim>(gd, c, ct, ubefore[k], ubefore[k + 1], cl, L, g, slice);
+    c = run_group<Dim>(gd, c, ct, ubefore[k], ubefore[k + 1], cl, L, g, slice);
   }
   // every wavefront has made its last claim once `done` reaches the launch's
   // wavefront count: the last one resets both counters for the next launch
@@ -433,13 +436,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void kron_grouped2d_kernel(
     const uint8_t* __restrict__ ws, int64_t header_off) {
   __shared__ __attribute__((aligned(16))) float slices[kBlock / kWave][kGroupSlice2];
-  grouped_phase<ModeBF16x3, 2>(ws, reinterpret_cast<const Header*>(ws + header_off), slices[threadIdx.x >> 6]);
+  grouped_phase<2>(ws, reinterpret_cast<const Header*>(ws + header_off), slices[threadIdx.x >> 6]);
 }
 
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void kron_grouped3d_kernel(
     const uint8_t* __restrict__ ws, int64_t header_off) {
   __shared__ __attribute__((aligned(16))) float slices[kBlock / kWave][kGroupSlice3];
-  grouped_phase<ModeBF16x3, 3>(ws, reinterpret_cast<const Header*>(ws + header_off), slices[threadIdx.x >> 6]);
+  grouped_phase<3>(ws, reinterpret_cast<const Header*>(ws + header_off), slices[threadIdx.x >> 6]);
 }
 
 // Both bf16x3 phases in one launch: a share of the wavefronts (split16 of
@@ -451,11 +454,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
   const int wave = (int)((blockIdx.x * kBlock + threadIdx.x) >> 6);
   float* slice = slices[threadIdx.x >> 6];
   if ((wave & 15) < h->split16) {
-    grouped_phase<ModeBF16x3, 2>(ws, h, slice);
-    grouped_phase<ModeBF16x3, 3>(ws, h, slice);
+    grouped_phase<2>(ws, h, slice);
+    grouped_phase<3>(ws, h, slice);
   } else {
-    grouped_phase<ModeBF16x3, 3>(ws, h, slice);
-    grouped_phase<ModeBF16x3, 2>(ws, h, slice);
+    grouped_phase<3>(ws, h, slice);
+    grouped_phase<2>(ws, h, slice);
   }
 }
 
@@ -635,7 +638,7 @@ struct Phases {
 };
 
 // FP32: workgroups in proportion to the groups' costs, at most one per unit,
-// kOversubscribe times as many as are resident (2: 375, 4: 362, 8: 371, 16: 406
+// kOversubscribe times as many as are resident (2: 305, 4: 293, 8: 299, 16: 328
 // us for 500,000 mixed operands, where a workgroup's factor loads come to cost
 // too much).  2-D first: its latency-bound units then overlap the 3-D ones
 // (at the end: 10 us more); in each dimension the costliest units first, so

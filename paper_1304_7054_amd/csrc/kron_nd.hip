@@ -729,7 +729,7 @@ constexpr int fuse_blocks() {
 // 8 (in elements of 1, 2 or 4 words: 4 mod 8, 2 mod 4, odd).
 int fuse_pitch(int f, size_t elem) {
   const int w = (int)(elem / 4), mod = 8 / w, want = 4 / w;
-  return mod >= 2 ? f + ((want - f) % mod + mod) % mod : f | 1;
+  return f + ((want - f) % mod + mod) % mod;
 }
 
 // Plan of the products over indices k0 .. d - 1 as one kernel; false when they
@@ -916,7 +916,7 @@ void fuse_run(const FusedArgs& P, int ks, size_t lds, bool beta, T ar, T ai, T b
   constexpr int kCB = fuse_blocks<T, kC>();
   if (ks <= 4) fuse_launch<T, kC, 4, kCB>(P, lds, beta, ar, ai, br, bi, stream);
   else if (ks <= 8) fuse_launch<T, kC, 8, kCB>(P, lds, beta, ar, ai, br, bi, stream);
-  else fuse_launch<T, kC, 16, kCB>(P, lds, beta, ar, ai, br, bi, stream);
+  else if constexpr (!kC) fuse_launch<T, kC, 16, kCB>(P, lds, beta, ar, ai, br, bi, stream);  // complex: ks <= 8
 }
 
 // Whether the strides (none: yes) are those of packed operands.

@@ -24,7 +24,7 @@ namespace {
 // op(M) with leading dimension ld, alpha on the first factor, written dense
 // (factor f at out + f * n^2, column-major).
 template <typename T>
-__global__ __launch_bounds__(256) void prepare_strided_factors_kernel(int n, int nf, const T* __restrict__ A, int lda,
+__global__ __launch_bounds__(256) void prepare_factors_kernel(int n, int nf, const T* __restrict__ A, int lda,
                                                                       const T* __restrict__ B, int ldb,
                                                                       const T* __restrict__ C, int ldc, unsigned tmask,
                                                                       T alpha, T* __restrict__ out) {
@@ -418,8 +418,7 @@ int strided_call(int dim, int n, const char* ops, typename M::io_t alpha, const 
   if (!ws || reinterpret_cast<uintptr_t>(ws) % sizeof(T) != 0) return -(kBatch + 1);
   if (ws_bytes < (size_t)dim * n * n * sizeof(T)) return -(kBatch + 2);
   T* P = static_cast<T*>(ws);
-  hipLaunchKernelGGL(prepare_strided_factors_kernel<T>, dim3(1), dim3(256), 0, stream, n, dim, mats[0], lds[0],
-                     mats[1], lds[1], dim == 3 ? mats[2] : mats[1], dim == 3 ? lds[2] : lds[1], tmask, alpha, P);
+  prepare_factors(n, dim, mats, lds, tmask, alpha, P, stream);
   const Strides xs{ldx[0], dim == 3 ? ldx[1] : 0, ldx[dim - 1]};
   const Strides ys{ldy[0], dim == 3 ? ldy[1] : 0, ldy[dim - 1]};
   const T *PA = P, *PB = P + n * n, *PC = P + (dim - 1) * n * n;
@@ -436,12 +435,12 @@ int strided_call(int dim, int n, const char* ops, typename M::io_t alpha, const 
 
 void prepare_factors(int n, int nf, const float* const* F, const int* ld, unsigned tmask, float alpha, float* out,
                      hipStream_t stream) {
-  hipLaunchKernelGGL(prepare_strided_factors_kernel<float>, dim3(1), dim3(256), 0, stream, n, nf, F[0], ld[0], F[1],
+  hipLaunchKernelGGL(prepare_factors_kernel<float>, dim3(1), dim3(256), 0, stream, n, nf, F[0], ld[0], F[1],
                      ld[1], F[nf - 1], ld[nf - 1], tmask, alpha, out);
 }
 void prepare_factors(int n, int nf, const double* const* F, const int* ld, unsigned tmask, double alpha, double* out,
                      hipStream_t stream) {
-  hipLaunchKernelGGL(prepare_strided_factors_kernel<double>, dim3(1), dim3(256), 0, stream, n, nf, F[0], ld[0], F[1],
+  hipLaunchKernelGGL(prepare_factors_kernel<double>, dim3(1), dim3(256), 0, stream, n, nf, F[0], ld[0], F[1],
                      ld[1], F[nf - 1], ld[nf - 1], tmask, alpha, out);
 }
 
