@@ -62,8 +62,8 @@ enum kron_mode {
                            products hi*hi' + hi*lo' + lo*hi' on bf16 matrix cores,
                            FP32 sums */
   KRON_MODE_BF16 = 3,   /* bf16 storage of A, B, C, X, Y (uint16_t bit patterns),
-                           FP32 sums, intermediates kept as bf16 hi + lo pairs,
-                           output rounded to nearest even */
+                           FP32 sums, intermediates kept as bf16 hi + lo pairs or
+                           in FP32, output rounded to nearest even */
   KRON_MODE_BF16X6 = 4  /* FP32 in/out; each FP32 value split three ways into bf16
                            h + m + l (all 24 bits), six bf16 products per FP32 product
                            (terms below 2^-23 dropped), FP32 sums */
@@ -249,9 +249,10 @@ typedef struct kron_c64 {
    matrix of operand p starts at factors[k] + p * ldfp[k] elements (ldfp[k]
    = 0: one matrix for the whole batch).  1 <= m[k], n[k] <= 65536,
    1 <= d <= 8.  beta == 0 does not read Y.  X and Y must not overlap.
-   Computed as d mode products (fastest index first), each one pass over
-   device memory through the caller's workspace `ws` (16-byte aligned, at
-   least kron_nd_workspace_size(d, m, n, batch, type) bytes; none for d = 1)
+   Computed as d mode products, those that fit in one kernel on operands in
+   on-chip memory, the others one pass over device memory each through the
+   caller's workspace `ws` (16-byte aligned, at least
+   kron_nd_workspace_size(d, m, n, batch, type) bytes; none for d = 1)
    with type KRON_MODE_F32, KRON_MODE_F64, KRON_TYPE_C32 or KRON_TYPE_C64.
    With that workspace an operand's result does not depend, to the last bit,
    on the batch it is in.
@@ -276,9 +277,8 @@ int kron_nd_batched_c64(int d, const int* m, const int* n, const char* ops, kron
 
 /* Section 3's TKRON1 / TKRON2 / TKRON3 argument lists with rectangular
    factors, leading dimensions, op in {N, T, C}, alpha, beta, and the types
-   S, D, C, Z of the paper (f32, f64, c32, c64), on the engine above (one
-   pass per dimension; the first pass reads the strided X, the last writes
-   the strided Y).  Factor roles are this library's: A acts on the slowest
+   S, D, C, Z of the paper (f32, f64, c32, c64), on the kernels above, which
+   read the strided X and write the strided Y.  Factor roles are this library's: A acts on the slowest
    index of each operand, B on the fastest (2-D) or the middle one (3-D), C
    on the fastest (3-D), i.e. these compute the paper's K(B, A) and K(C, B, A)
    in its index naming.
@@ -398,8 +398,9 @@ int kron3d_batched_ex_f32_noalloc(int n, char opA, char opB, char opC, float alp
    _ex entry points; opX (2-D) transposes each operand.  Any stride and any
    element-aligned address is accepted: elements are read and written one at
    a time, except in 3-D with n = 16 when every X and Y stride is a multiple
-   of 4 elements and both bases are 16-byte aligned (then 16-byte vectors).
-   Contiguous arrays run faster through the _ex entry points.  Returns 0 or -k (argument k invalid; positions beyond 15 are
+   of 4 elements and both bases are 16-byte aligned (then 16-byte vectors, but
+   for FP64 with beta = 0).  Contiguous arrays run faster through the _ex entry
+   points.  Returns 0 or -k (argument k invalid; positions beyond 15 are
    reported by kron_status_string as "invalid argument"). */
 int kron2d_batched_strided_f32(int n, char opA, char opB, char opX, float alpha, const float* A, int lda,
                                const float* B, int ldb, const float* X, int64_t ldx, int64_t ldxp, float beta,
@@ -557,8 +558,8 @@ int kron_copy_bytes(const void* src, void* dst, size_t bytes, hipStream_t stream
 int kron_set_launch(int mode, int dim, int n, int blocks_per_cu, int variant);
 int kron_get_launch(int mode, int dim, int n, int* blocks_per_cu, int* variant);
 
-/* Autotuner: time every launch shape (variants x 0..4 workgroups per CU) of
-   (mode, dim, n) on the caller's device buffers (A, B, C, X read; Y is
+/* Autotuner: time every launch shape (variants x 0..4 workgroups per CU, and the
+   built-in default) of (mode, dim, n) on the caller's device buffers (A, B, C, X read; Y is
    overwritten; C may be NULL for dim 2; element type as for the mode's
    entry points), `reps` timed launches each on `stream` with HIP events, in
    three sweeps over all shapes (forward, reverse, forward; three untimed

@@ -9,9 +9,11 @@
 
 namespace kron {
 
-// Partial sums a call may leave in its workspace: a fixed function of the
-// batch and the device.
-int64_t grad_waves(int dim, int n, int64_t batch) {
+// Workgroups a call may have, each with one partial sum of every gradient in the
+// workspace: a fixed function of the batch and the device.  One for (16 / n)^dim
+// operands and a multiple of four, at most eight a CU; at n <= 4 that is fewer
+// than there are tiles in a small batch (3-D n = 2, 1 MiB of X: 64 for 512).
+int64_t grad_partials(int dim, int n, int64_t batch) {
   const int64_t q = 16 / n;
   const int64_t ops = dim == 3 ? q * q * q : q * q;
   const int64_t ntiles = (batch + ops - 1) / ops;
@@ -22,7 +24,7 @@ int64_t grad_waves(int dim, int n, int64_t batch) {
 }
 
 size_t grad_workspace_bytes(int dim, int n, int64_t batch, int elem_bytes) {
-  return (size_t)grad_waves(dim, n, batch) * 3 * 256 * (size_t)elem_bytes;
+  return (size_t)grad_partials(dim, n, batch) * 3 * 256 * (size_t)elem_bytes;
 }
 
 namespace {
@@ -34,7 +36,7 @@ unsigned backward_blocks(int64_t batch) {
   using S = Bwd<T, Dim, N>;
   const int64_t tiles = (batch + S::P - 1) / S::P;
   const int64_t cap = std::min((int64_t)device_cus() * occupancy_blocks(kron_backward_kernel<S>, S::kThreads),
-                               grad_waves(Dim, N, batch));
+                               grad_partials(Dim, N, batch));
   return (unsigned)std::min(tiles, cap);
 }
 

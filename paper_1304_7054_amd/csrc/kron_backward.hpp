@@ -180,11 +180,10 @@ struct BwdTiles {
       }
   }
 
-  // acc += sum over the columns of the tile's first `planes` planes (3-D slow
-  // axis: rows) of U(L, column) V(L, column).  The wavefronts take planes in
-  // turn.  A tile's columns are summed by themselves first, in two chains that
-  // keep the matrix pipe fed, so that the running sum grows by one rounding per
-  // tile instead of one per column.
+  // sum += sum over the columns of the tile's first `planes` planes (3-D slow
+  // axis: rows) of U(i, column) V(j, column), for all i and j.
+  // Up to n = 8 every column goes straight to a running sum: a lane's (n <= 4), or
+  // that of one of a wavefront's 16 column groups.
   template <int kAxis>
   __device__ __forceinline__ void contract(const T* U, const T* V, int planes, own_t& sum) const {
     regs_t u, v;
@@ -228,6 +227,9 @@ struct BwdTiles {
             sum.v[a][b] = __builtin_amdgcn_mfma_f32_4x4x1f32(u[a], v[b], sum.v[a][b], 0, 0, 0);
     }
   }
+  // n > 8: the wavefronts take planes in turn.  A tile's columns are summed by
+  // themselves first, in two chains that keep the matrix pipe fed, so that the
+  // running sum grows by one rounding per tile instead of one per column.
   template <int kAxis>
   __device__ __forceinline__ void contract(const T* U, const T* V, int planes, acc_t& sum) const {
     acc_t acc[2] = {acc_t{0, 0, 0, 0}, acc_t{0, 0, 0, 0}};

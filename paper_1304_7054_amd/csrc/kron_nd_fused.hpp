@@ -21,7 +21,8 @@
 
 namespace kron {
 
-// q = x / d for x < 2^31, by multiplication.
+// q = x / d for x < 2^31, by multiplication with a rounded-up reciprocal
+// (Granlund and Montgomery, Division by invariant integers, 1994, figure 4.1).
 struct FastDiv {
   uint32_t d, m, s;
   __device__ __forceinline__ uint32_t div(uint32_t x) const { return (__umulhi(x, m) + x) >> s; }
@@ -206,9 +207,9 @@ __device__ __forceinline__ void fused_stage(const FusedStage& st, typename Fused
   }
 }
 
-// kKS: the largest product's steps of four contracted indices.
 // Wavefronts per SIMD the registers are held to, by measurement (256 MiB and
-// more of operands; two fewer or more cost 5 to 30 %).
+// more of operands; two fewer or more cost 5 to 30 %).  kKS: the largest
+// product's steps of four contracted indices.
 template <typename T, bool kC, int kKS>
 constexpr int fused_waves() {
   if (kKS > 8) return 2;

@@ -106,7 +106,7 @@ int grouped_launch(const void* ws, hipStream_t stream);
 // The backward with at least one factor gradient (kron_backward.hip): dX (may
 // be null) and the factor gradients (null ones are skipped; dC only in 3-D) in
 // one pass over X and dY.  ws holds grad_workspace_bytes().
-int64_t grad_waves(int dim, int n, int64_t batch);
+int64_t grad_partials(int dim, int n, int64_t batch);
 size_t grad_workspace_bytes(int dim, int n, int64_t batch, int elem_bytes);
 int backward(const struct kron_group_grad& d, void* ws, hipStream_t stream);
 // The same for each of several groups (descriptor, workspace), in few launches.

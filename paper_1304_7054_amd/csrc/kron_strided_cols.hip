@@ -1,5 +1,6 @@
-// Strided storage, n < 16: the mode products of the column kernels with the
-// strides only where the operands enter and leave.
+// Strided storage: the mode products of the column kernels with the strides only
+// where the operands enter and leave (n < 16; n = 16 where the general kernel's
+// 16-byte rows do not apply or, FP64 3-D, are the slower ones).
 //
 // A workgroup holds P operands packed in LDS (the image of the backward
 // kernels) and works on one column per lane, so that no lane, product or
@@ -24,7 +25,7 @@
 namespace kron {
 namespace {
 
-constexpr unsigned kNear = 1u << 29;  // elements; twice the bytes of FP64 stay below 2^32
+constexpr unsigned kNear = 1u << 29;  // elements; offsets stay below it, and their bytes in FP64 below 2^32
 
 // The result's bytes, gaps included, up to which its lines wait in the last
 // cache for their neighbours; beyond, stores that bypass it are faster (n = 10
