@@ -52,6 +52,34 @@ def test_varying_factors(tag, shape):
             assert np.linalg.norm(got - want) <= TOL[tag] * np.linalg.norm(want), (batch, ops, beta)
 
 
+# batches that give every workgroup tiles of several operands, or of several
+# slices of one operand (20^3 and 24^3), and end inside a tile
+FULL = [([2, 33], [33, 2], 3001), ([17, 17], [16, 16], 2077), ([16, 16], [16, 16], 3500), ([40, 3], [36, 5], 2600),
+        ([20, 20, 20], [20, 20, 20], 131), ([24, 24, 24], [24, 24, 24], 90), ([3, 20, 20], [2, 24, 20], 700)]
+
+
+@pytest.mark.parametrize("shape", range(len(FULL)))
+@pytest.mark.parametrize("tag", list(DT))
+def test_varying_factors_in_full_tiles(tag, shape):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    m, n, batch = FULL[shape]
+    d, nx, ny = len(m), int(np.prod(n)), int(np.prod(m))
+    rng = np.random.default_rng(90 + shape)
+    ops = "".join(rng.choice(list("NTC"), d))
+    ldfp = [a * b + 3 * k for k, (a, b) in enumerate(zip(m, n))]
+    fac = [_draw(rng, tag, batch * p) for p in ldfp]
+    X = _draw(rng, tag, batch * nx)
+    ty = torch.full((batch * ny,), float("nan"), dtype=DT[tag], device="cuda")
+    getattr(kron, f"kron_nd_batched_{tag}")(m, n, ops, 1.0, [torch.from_numpy(f).cuda() for f in fac],
+                                            torch.from_numpy(X).cuda(), 0.0, ty, batch, ldfp=ldfp)
+    torch.cuda.synchronize()
+    want = oracle.kron_nd(m, n, ops, 1.0, fac, X, 0.0, np.zeros(batch * ny), batch, ldfp=ldfp)
+    got = ty.cpu().numpy()
+    assert np.all(np.isfinite(got)), ops
+    assert np.linalg.norm(got - want) <= TOL[tag] * np.linalg.norm(want), ops
+
+
 def test_many_small_operands_share_workgroups():
     """700,000 2 x 2 operands take less time than three 1 GiB copies; with a
     workgroup each they took six."""
