@@ -787,7 +787,7 @@ bool fuse_plan(int d, int k0, const int* m, const int* n, const int* opc, const 
   // where the rounds saved outweigh the workgroups that a CU then holds (256 MiB,
   // complex 16 x 16 to 17 x 17: 375 us within kFuseTile, 320 beyond; without the
   // condition FP32 2 x 2 3,160 and 3,820, 64 x 4 236 and 274).
-  const int64_t room = slices / (2 * device_cus());
+  const int64_t room = std::min(slices / (2 * device_cus()), (int64_t)(((double)kFuseLds - shared) / one));
   const int64_t fill = std::max<int64_t>(1, std::min((int64_t)((double)kFuseTile / one), room));
   const int64_t most = std::max(fill, std::min((int64_t)((double)(per_op ? 2 * kFuseTile : kFuseTile) / one), room));
   auto per_cu = [&](int64_t o) { return std::floor(std::min(8.0, 160.0 * 1024 / (shared + (double)o * one))); };
