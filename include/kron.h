@@ -399,8 +399,10 @@ int kron3d_batched_ex_f32_noalloc(int n, char opA, char opB, char opC, float alp
    element-aligned address is accepted: elements are read and written one at
    a time, except in 3-D with n = 16 when every X and Y stride is a multiple
    of 4 elements and both bases are 16-byte aligned (then 16-byte vectors, but
-   for FP64 with beta = 0).  Contiguous arrays run faster through the _ex entry
-   points.  Returns 0 or -k (argument k invalid; positions beyond 15 are
+   for FP64 with beta = 0).  For FP32, n = 16 and rows that such vectors cannot
+   take, the last bits depend on whether Y spans more than 320 MiB (the axes are
+   then contracted in another order).  Contiguous arrays run faster through the
+   _ex entry points.  Returns 0 or -k (argument k invalid; positions beyond 15 are
    reported by kron_status_string as "invalid argument"). */
 int kron2d_batched_strided_f32(int n, char opA, char opB, char opX, float alpha, const float* A, int lda,
                                const float* B, int ldb, const float* X, int64_t ldx, int64_t ldxp, float beta,
