@@ -36,6 +36,10 @@ inline FastDiv fast_div(uint32_t d) {
 
 constexpr int kFuseMax = 8;
 
+// Whose factors a tile has: the batch's, each operand's own, or those of the one
+// operand that it is, or has slices of.
+enum FusedFactors { kFusedShared, kFusedOwn, kFusedOne };
+
 // One product: columns c = (u, w) with w < post; element k of a column is at
 // u * in_u + where(w) + k * in_s, where(w) = (w / fast) * pitch + w % fast.
 struct FusedStage {
@@ -217,7 +221,7 @@ constexpr int fused_waves() {
   return sizeof(T) == 4 ? 5 : kKS <= 4 ? 4 : 3;
 }
 
-template <typename T, bool kC, int kKS, int kCB, bool kBeta, bool kVar>
+template <typename T, bool kC, int kKS, int kCB, bool kBeta, int kVar>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fused_waves<T, kC, kKS>()))) void kron_nd_fused_kernel(
     FusedArgs P, FastDiv xe, FastDiv ye, T ar, T ai, T br, T bi) {
   using elem_t = typename FusedElem<T, kC>::type;
@@ -234,7 +238,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fused_waves
       const FusedStage st = P.st[q];
       const T* F = static_cast<const T*>(st.F) + operand * st.ldfp * kS;
       for (int e = tid; e < count * (int)st.frags.d * 64; e += 256) {
-        const uint32_t f = e >> 6, op = kVar ? st.frags.div(f) : 0, h = f - op * st.frags.d, rb = st.steps.div(h);
+        const uint32_t f = e >> 6, op = kVar == kFusedOwn ? st.frags.div(f) : 0, h = f - op * st.frags.d, rb = st.steps.div(h);
         const int i = 16 * rb + (e & 15), k = 4 * (h - rb * st.steps.d) + ((e >> 4) & 3);
         T re = 0, im = 0;
         if (i < st.m && k < st.n) {
@@ -248,7 +252,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fused_waves
       }
     }
   };
-  if constexpr (!kVar) load_factors(0, 1);
+  if constexpr (kVar == kFusedShared) load_factors(0, 1);
   // where each column of a full tile starts in the images, for every product
   uint32_t* const tab = P.table < 0 ? nullptr : reinterpret_cast<uint32_t*>(fused_lds + P.table);
   if (tab) {
@@ -270,11 +274,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fused_waves
     const uint32_t row = P.x.ext[0].div(e);
     *in_lds(reinterpret_cast<vec_t*>(img + row * P.x.pitch + (e - row * P.x.ext[0].d))) = v;
   };
-  // a workgroup's tiles; slices of operands with factors of their own one after
-  // the other, so that the factors are read once per operand
-  const bool own = kVar && P.per == 1;
+  // a workgroup's tiles; slices of an operand with its own factors one after the
+  // other, so that the factors are read once per operand
   int64_t t = blockIdx.x, end = P.ntiles, step = gridDim.x, loaded = -1;
-  if (kVar && !own) {
+  if (kVar == kFusedOne && P.per > 1) {
     const int64_t share = (P.ntiles + gridDim.x - 1) / gridDim.x;
     t = blockIdx.x * share;
     end = t + share < P.ntiles ? t + share : P.ntiles;
@@ -285,9 +288,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fused_waves
     const int nops = (int)(rem < P.ops ? rem : P.ops);
     const elem_t* X = static_cast<const elem_t*>(P.X) + t * P.ops * (P.x.stride[0] < 0 ? P.x.elems : P.x.sp);
     elem_t* Y = static_cast<elem_t*>(P.Y) + t * P.ops * (P.y.stride[0] < 0 ? P.y.elems : P.y.sp);
-    if constexpr (kVar) {
-      const int64_t operand = own ? t * P.ops : t * P.ops / P.per;
-      if (operand != loaded) load_factors(operand, own ? nops : 1);
+    if constexpr (kVar == kFusedOwn) load_factors(t * P.ops, nops);
+    if constexpr (kVar == kFusedOne) {
+      const int64_t operand = P.per > 1 ? t * P.ops / P.per : t;
+      if (operand != loaded) load_factors(operand, 1);
       loaded = operand;
     }
     {
@@ -326,8 +330,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fused_waves
       const FusedStage st = P.st[q];
       static_for<kKS>([&](auto i) {
         constexpr int kSteps = decltype(i)::value + 1;
-        if (st.ks == kSteps) fused_stage<T, kC, kSteps, kSteps <= 8 ? kCB : 1, kVar>(
-              st, base, tab, own ? nops : 1, own ? st.cols : nops * st.cols, P.facs, wave, lane);
+        if (st.ks == kSteps) fused_stage<T, kC, kSteps, kSteps <= 8 ? kCB : 1, kVar == kFusedOwn>(
+              st, base, tab, nops, kVar == kFusedOwn ? st.cols : nops * st.cols, P.facs, wave, lane);
       });
       lds_barrier();
     }
